@@ -370,7 +370,7 @@ int32_t co3_user_encode(const float *g, float *err, int64_t n, int32_t U, int64_
     // the codes (after a resident grid: with the ragged end of the vector and the partial count tables added
     // up, in the same launch), then the compression
     const hipError_t e = coop ? co3_launch_user_finish(g, err, symbuf, n, co3_coop_full_elements(n, kpt), stride, U,
-                                                       nseg > 1 ? seg_off : nullptr, nseg, anchor, gamma, fmt, nib, counts_rep, CO3_COOP_COUNT_REPS, counts, codes, status, st, 0, U)
+                                                       nseg > 1 ? seg_off : nullptr, nseg, anchor, gamma, fmt, nib, counts_rep, counts, codes, status, st, 0, U)
                               : co3_launch_build_code(counts, U, fc.K, codes, status, st);
     if (e != hipSuccess) return CO3_EHIP;
     return hip_rc(co3_launch_encode(symbuf, n, U, stride, codes, fc.K, nullptr, 1, words, cap_words, chunk_syms, chunk_bitoff,
