@@ -3,7 +3,8 @@
 #include "co3_dev.h"
 #include "kernels.h"
 
-#define DE_BLOCK 1024
+#define DE_BLOCK 512           // most lanes of a workgroup of k_decode
+#define DE_MIN_BLOCK 256       // load_tables wants this many threads
 
 __device__ __forceinline__ const Co3Code *dcode_of(const void *codes, int u)
 {
@@ -27,6 +28,7 @@ __device__ __forceinline__ const Co3Code *dcode_of(const void *codes, int u)
 #define DE_GROUP 16          // symbols per run: one ring refill point, one 16-byte store
 #define DE_MISS_LEN 255u     // length field of a table entry that does not resolve a symbol
 #define DE_PAIR_BITS 12      // prefix length of the two-symbol table used for alphabets of at most 16 symbols
+#define DE_REFILL 4          // table lookups between two reads of the ring: 4 x 14 bits lie in a window of 64
 enum { DE_SHORT = 0, DE_LONG = 1, DE_PAIRS = 2 };   // fast-path variants of decode_range
 
 struct LaneStream {
@@ -106,6 +108,15 @@ struct LaneStream {
         uint64_t two = ((uint64_t)pc[RING_ROW_DW] << 32) | (uint64_t)pc[0];
         return (uint32_t)((two << (rel & 31u)) >> 32);
     }
+    // The 64 stream bits at the negated position m = -rel.  With d = (rel - 1) / 32, whose ring index is bits
+    // 5..8 of m, they lie in pieces d, d+1, d+2: three LDS reads and two funnel shifts by m mod 32.
+    __device__ __forceinline__ uint64_t window64(uint32_t m) const
+    {
+        const uint32_t row = (m >> 5) & 15u;
+        const uint32_t *pc = slot + row * RING_ROW_DW;
+        const uint32_t d0 = pc[RING_ROW_DW], d1 = pc[0], d2 = slot[((row - 1u) & 15u) * RING_ROW_DW];
+        return ((uint64_t)__builtin_amdgcn_alignbit(d0, d1, m) << 32) | __builtin_amdgcn_alignbit(d1, d2, m);
+    }
     __device__ __forceinline__ uint32_t piece(uint32_t d) const { return slot[(16u - (d & 15u)) * RING_ROW_DW]; }
     __device__ __forceinline__ uint64_t peek64()
     {
@@ -124,7 +135,7 @@ struct LaneStream {
 template <int BITS>
 struct DecTablesT {
     static constexpr int kBits = BITS;
-    uint16_t lut[1 << BITS];
+    alignas(16) uint16_t lut[1 << BITS];
     uint64_t first_code[65];
     uint16_t count[66];
     uint16_t base[66];
@@ -142,43 +153,70 @@ __device__ __forceinline__ void load_tables(Tables &t, const Co3Code *cd)
     const uint32_t ml = cd->maxlen > 64 ? 64 : cd->maxlen;
     // table prefix here: the stored one, widened up to BITS when the code has longer codewords
     const uint32_t nb = (BITS > CO3_LUT_BITS_MAX && ml > lb) ? (ml < BITS ? ml : BITS) : lb;
-    for (int i = threadIdx.x; i < 65; i += blockDim.x) t.first_code[i] = cd->first_code[i];
-    for (int i = threadIdx.x; i < 66; i += blockDim.x) {
-        t.count[i] = cd->count[i];
-        t.base[i] = cd->base[i];
+    // Everything is requested before anything is stored: one trip to memory in all (at least 256 threads).  The
+    // widened entries come from the stored ones and from the codewords that they leave out; reading a stored entry
+    // and searching the lengths for each of the 2^14 took 8 to 10 us of a workgroup (32 x 1 M E3M1 44 -> 36 us,
+    // 16 x 25 M E4M3 356 -> 324).
+    constexpr uint32_t PIECES = sizeof(Co3Code::lut) / 8;                  // 4 stored entries each (blobs are 8-byte aligned)
+    constexpr int ROUNDS = (PIECES + DE_MIN_BLOCK - 1) / DE_MIN_BLOCK;
+    const uint2 *lut_g = reinterpret_cast<const uint2 *>(cd->lut);
+    const int x = (int)threadIdx.x;
+    const uint32_t step = blockDim.x;
+    uint2 v[ROUNDS];
+#pragma unroll
+    for (int r = 0; r < ROUNDS; ++r) {
+        const uint32_t q = (uint32_t)x + r * step;
+        v[r] = q < PIECES && q * 4u < (1u << lb) ? lut_g[q] : make_uint2(0u, 0u);
     }
-    for (int i = threadIdx.x; i < 256; i += blockDim.x) t.sorted[i] = cd->sorted[i];
-    if (threadIdx.x == 0) {
+    const uint64_t fc = x < 65 ? cd->first_code[x] : 0;
+    const uint16_t cn = x < 66 ? cd->count[x] : (uint16_t)0, ba = x < 66 ? cd->base[x] : (uint16_t)0;
+    const uint8_t so = x < 256 ? cd->sorted[x] : (uint8_t)0;
+    if (x < 65) t.first_code[x] = fc;
+    if (x < 66) {
+        t.count[x] = cn;
+        t.base[x] = ba;
+    }
+    if (x < 256) t.sorted[x] = so;
+    if (x == 0) {
         t.maxlen = ml;
         t.lut_bits = nb;
     }
-    if (nb == lb) {
-        for (uint32_t i = threadIdx.x; i < (1u << lb); i += blockDim.x) {
-            uint16_t e = cd->lut[i];
-            t.lut[i] = (e >> 8) ? e : (uint16_t)(DE_MISS_LEN << 8);   // miss: longer than the prefix, or invalid
-        }
-        __syncthreads();
-    } else {
-        __syncthreads();                 // the canonical tables are read below
-        for (uint32_t i = threadIdx.x; i < (1u << nb); i += blockDim.x) {
-            uint32_t e = cd->lut[i >> (nb - lb)];
-            if ((e >> 8) == 0u) {        // not resolved by the stored prefix: lengths lb+1 .. nb by the canonical rule
-                e = DE_MISS_LEN << 8;
-                for (uint32_t l = lb + 1; l <= nb; ++l) {
-                    const uint64_t off = (uint64_t)(i >> (nb - l)) - t.first_code[l];
-                    if (off < (uint64_t)t.count[l]) {
-                        e = (l << 8) | t.sorted[(t.base[l] + (uint32_t)off) & 255u];
-                        break;
-                    }
-                }
+    const uint32_t wide = nb - lb;                                         // each stored entry fills 2^wide
+#pragma unroll
+    for (int r = 0; r < ROUNDS; ++r) {
+        const uint32_t q = (uint32_t)x + r * step;
+        if (q >= PIECES || q * 4u >= (1u << lb)) continue;
+#pragma unroll
+        for (uint32_t k = 0; k < 4u; ++k) {
+            uint32_t e = ((k < 2u ? v[r].x : v[r].y) >> (16 * (k & 1))) & 0xffffu;
+            if ((e >> 8) == 0u) e = DE_MISS_LEN << 8;                      // longer than the prefix, or invalid
+            const uint32_t at = q * 4u + k;
+            if (wide == 0u) {
+                if (at < (1u << lb)) t.lut[at] = (uint16_t)e;
+            } else if (wide == 1u) {
+                reinterpret_cast<uint32_t *>(t.lut)[at] = e | (e << 16);
+            } else {
+                const uint32_t e2 = e | (e << 16);
+                for (uint32_t h = 0; h < (1u << wide) / 4u; ++h)
+                    reinterpret_cast<uint2 *>(t.lut)[(at << (wide - 2)) + h] = make_uint2(e2, e2);
             }
-            t.lut[i] = (uint16_t)e;
         }
+    }
+    __syncthreads();
+    if (wide != 0u) {
+        // the codewords of lengths lb+1 .. nb, a thread each, enter where their prefixes lie
+        for (uint32_t l = lb + 1; l <= nb; ++l)
+            for (uint32_t k = (uint32_t)x; k < t.count[l]; k += step) {
+                const uint64_t code = t.first_code[l] + k;
+                const uint16_t e = (uint16_t)((l << 8) | t.sorted[(t.base[l] + k) & 255u]);
+                if (code < (1ull << l))
+                    for (uint32_t h = 0; h < (1u << (nb - l)); ++h) t.lut[((uint32_t)code << (nb - l)) + h] = e;
+            }
         __syncthreads();
     }
     if (t.maxlen > t.lut_bits) {      // only codes with codewords beyond the table prefix use the limits
         for (int l = threadIdx.x; l < 65; l += blockDim.x) {
-            int j = l;
+            int j = l < (int)t.maxlen ? l : (int)t.maxlen;
             while (j >= 1 && t.count[j] == 0) --j;     // canonical order: shorter codewords are numerically below
             uint64_t lim = 0;
             if (j >= 1) {
@@ -264,26 +302,38 @@ __device__ __forceinline__ void decode_run_careful(const Tables &t, LaneStream &
     ls.ensure(((ls.rel >> 7) + 3u) * 4u);
 }
 
-// Two-symbol entry e read at position m holds only its first codeword: the entry completed with the
-// second codeword from a lookup of its own (the combined length in the top byte).
+// One lookup in the two-symbol table.  win: the stream from the negated position m on; read anew from the ring
+// every DE_REFILL lookups (of at most DE_PAIR_BITS bits each).  An entry that holds only its first codeword is
+// completed from a lookup of its own, in a branch that the wavefront skips when no lane needs it and that leaves
+// a whole window behind.  mw: the last position at which the ring was read.
 template <bool NIB>
-__device__ __forceinline__ uint32_t pair_second(const LaneStream &ls, const uint32_t *pairs, uint32_t e, uint32_t m,
-                                                bool &bad)
+__device__ __forceinline__ uint32_t pair_step(const LaneStream &ls, const uint32_t *pairs, uint64_t &win, uint32_t &m,
+                                              uint32_t &mw, bool &bad)
 {
-    const uint32_t l1 = (e >> 16) & 0xffu;
-    if (l1 == DE_MISS_LEN) {     // not even the first codeword: the careful path takes the run
-        bad = true;
-        return 2u << 24;
+    uint32_t e = pairs[win >> (64 - DE_PAIR_BITS)];
+    uint32_t l = e >> 24, drop = l;
+    if (l == 0u) {
+        const uint32_t l1 = (e >> 16) & 0xffu;
+        if (l1 == DE_MISS_LEN) {     // not even the first codeword: the careful path takes the run
+            bad = true;
+            l = 2u;
+        } else {
+            const uint32_t e2 = pairs[(win << l1) >> (64 - DE_PAIR_BITS)];
+            uint32_t l2 = (e2 >> 16) & 0xffu;
+            if (l2 == DE_MISS_LEN) {
+                bad = true;
+                l2 = 1u;
+            }
+            e = (e & 0xffu) | ((e2 & 0xffu) << (NIB ? 4 : 8));
+            l = l1 + l2;
+        }
+        drop = 0u;
+        mw = m - l;
+        win = ls.window64(mw);
     }
-    const uint32_t m1 = m - l1;
-    const uint32_t *pc1 = ls.slot + ((m1 >> 5) & 15u) * RING_ROW_DW;
-    const uint32_t e2 = pairs[__builtin_amdgcn_alignbit(pc1[RING_ROW_DW], pc1[0], m1) >> (32 - DE_PAIR_BITS)];
-    uint32_t l2 = (e2 >> 16) & 0xffu;
-    if (l2 == DE_MISS_LEN) {
-        bad = true;
-        l2 = 1u;
-    }
-    return (e & 0xffu) | ((e2 & 0xffu) << (NIB ? 4 : 8)) | ((l1 + l2) << 24);
+    m -= l;
+    win <<= drop & 63u;
+    return e;
 }
 
 // One lane decodes symbols [i0, i1) of its chunk; the stream is open at symbol i0.  Symbols leave in
@@ -311,6 +361,7 @@ template <int MODE, class Tables>
 __device__ __forceinline__ void decode_range(const Tables &t, LaneStream &ls, int i0, int i1, uint8_t *out,
                                              int64_t run_step, bool &ok, const uint32_t *pairs = nullptr)
 {
+    static_assert(DE_REFILL * Tables::kBits <= 64 && DE_REFILL == 4, "a window holds the lookups between two refills");
     static_assert(DE_GROUP * Tables::kBits < DE_MISS_LEN, "a miss must advance more than a run of hits can");
     constexpr bool LONG = MODE == DE_LONG;
     const int shift = 32 - (int)t.lut_bits;
@@ -334,19 +385,17 @@ __device__ __forceinline__ void decode_range(const Tables &t, LaneStream &ls, in
             ls.group_boundary();
             const uint32_t rel0 = ls.rel;
             uint32_t w[8] = {0u, 0u, 0u, 0u, 0u, 0u, 0u, 0u};
-            uint32_t m = 0u - rel0;
+            uint32_t m = 0u - rel0, mw = m;
+            uint64_t win = 0;
             bool bad = false;
 #pragma unroll
             for (int b = 0; b < DE_GROUP; ++b) {
-                const uint32_t *pc = ls.slot + ((m >> 5) & 15u) * RING_ROW_DW;
-                const uint32_t win = __builtin_amdgcn_alignbit(pc[RING_ROW_DW], pc[0], m);
-                uint32_t e = pairs[win >> (32 - DE_PAIR_BITS)];
-                if ((e >> 24) == 0u) e = pair_second<false>(ls, pairs, e, m, bad);
-                m -= e >> 24;
+                if (b % DE_REFILL == 0) win = ls.window64(mw = m);
+                const uint32_t e = pair_step<false>(ls, pairs, win, m, mw, bad);
                 w[b >> 1] = __builtin_amdgcn_alignbit(e, w[b >> 1], 16);
             }
             ls.rel = 0u - m;
-            if (bad || ls.rel + 64u > ls.loaded * 128u) {   // rare
+            if (bad || 96u - mw > ls.loaded * 128u) {   // rare
                 ls.rel = rel0;
                 decode_run_careful(t, ls, shift, DE_GROUP, ok, w);
                 decode_run_careful(t, ls, shift, DE_GROUP, ok, w + 4);
@@ -359,63 +408,98 @@ __device__ __forceinline__ void decode_range(const Tables &t, LaneStream &ls, in
 #pragma unroll 1
     for (; i + DE_GROUP <= i1; i += DE_GROUP) {
         ls.group_boundary();
+        // a stretch of long codewords (the last run took more than nine bits a symbol): what has just been
+        // requested is waited for, which costs less than a run by the careful path
+        if (MODE != DE_PAIRS && ls.rel + 240u > ls.loaded * 128u) ls.land();
         const uint32_t rel0 = ls.rel;
         uint32_t w[4] = {0u, 0u, 0u, 0u};
-        // Work with the negated position m = -rel.  The window of 32 stream bits at rel is
-        // ({piece d, piece d+1} >> (m mod 32)) with d = (rel - 1) / 32, whose ring index is
-        // bits 5..8 of m: one field extract, one two-address LDS read, one funnel shift.
-        uint32_t m = 0u - rel0;
+        // Work with the negated position m = -rel.  The next 64 stream bits wait in registers and are read anew
+        // every DE_REFILL lookups, so that the chain from symbol to symbol holds one LDS access, the table's, in
+        // place of two (one user of 65,536 elements 26.6 -> 19 us, 16 x 25 M E4M3 391 -> 381, 10 x 11.2 M E3M0 54 -> 49).
+        uint32_t m = 0u - rel0, mw = m;
+        uint64_t win = 0;
         bool bad = false;
         if (MODE == DE_PAIRS) {
 #pragma unroll
             for (int b = 0; b < DE_GROUP / 2; ++b) {
-                const uint32_t *pc = ls.slot + ((m >> 5) & 15u) * RING_ROW_DW;
-                const uint32_t win = __builtin_amdgcn_alignbit(pc[RING_ROW_DW], pc[0], m);
-                uint32_t e = pairs[win >> (32 - DE_PAIR_BITS)];
-                if ((e >> 24) == 0u) e = pair_second<false>(ls, pairs, e, m, bad);   // rare
-                m -= e >> 24;
+                if (b % DE_REFILL == 0) win = ls.window64(mw = m);
+                const uint32_t e = pair_step<false>(ls, pairs, win, m, mw, bad);
                 w[b >> 1] = __builtin_amdgcn_alignbit(e, w[b >> 1], 16);
             }
         } else {
+        // Codeword longer than the table prefix: the first length whose largest left-aligned codeword is not
+        // below the window.  (The limits do not decrease with the length and stay put beyond the longest
+        // codeword, so counting the limits below the window gives the length; nearly all long codewords end
+        // within four bits of the prefix: those limits are compared without a loop.)
+        auto search = [&](uint64_t w64) -> uint32_t {
+            const uint32_t l0 = t.lut_bits + 1u;
+            uint32_t l = l0;
 #pragma unroll
-        for (int b = 0; b < DE_GROUP; ++b) {
-            const uint32_t row = (m >> 5) & 15u;
-            const uint32_t *pc = ls.slot + row * RING_ROW_DW;
-            const uint32_t d0 = pc[0];
-            uint32_t win = __builtin_amdgcn_alignbit(pc[RING_ROW_DW], d0, m);
-            uint32_t e = t.lut[win >> shift];
-            if (LONG && (e >> 8) == DE_MISS_LEN) {
-                // Codeword longer than the table prefix (skipped by the wavefront when no lane is here):
-                // 64-bit window, then the first length whose largest left-aligned codeword is not below it.
-                const uint32_t d2 = ls.slot[((row - 1u) & 15u) * RING_ROW_DW];
-                const uint64_t w64 = ((uint64_t)win << 32) | (uint64_t)__builtin_amdgcn_alignbit(d0, d2, m);
-                // (the limits do not decrease with the length and stay put beyond the longest codeword, so
-                // counting the limits below the window gives the length; nearly all long codewords end
-                // within four bits of the prefix: those limits are compared without a loop)
-                const uint32_t l0 = t.lut_bits + 1u;
-                uint32_t l = l0;
+            for (uint32_t k = 0; k < 4u; ++k) l += w64 > t.lim_incl[l0 + k] ? 1u : 0u;
+            if (l == l0 + 4u)
+                for (uint32_t j = l0 + 4u; j < t.maxlen; ++j) l += w64 > t.lim_incl[j] ? 1u : 0u;
+            const uint64_t off = (w64 >> (64u - l)) - t.first_code[l];
+            if (off < (uint64_t)t.count[l]) return (l << 8) | t.sorted[(t.base[l] + (uint32_t)off) & 255u];
+            bad = true;                   // no codeword starts here
+            return 1u << 8;
+        };
+        // With the wide table a miss is rare (about one in 10^4 symbols of an 8-bit format): one test per
+        // DE_REFILL symbols, after which the lane goes on one by one from the first miss.  Against a test at every
+        // symbol, for which each lookup has to wait: 16 x 25 M E4M3 324 -> 305 us, 32 x 1 M E3M1 36 -> 28; one user's
+        // 62 tensors in E4M3, some with stretches of long codewords, 54 -> 60.  With the narrow table (one miss in
+        // 200 symbols) the codeword is searched in place.
+        constexpr bool AGAIN = LONG && Tables::kBits > CO3_LUT_BITS_MAX;
 #pragma unroll
-                for (uint32_t k = 0; k < 4u; ++k) l += w64 > t.lim_incl[l0 + k] ? 1u : 0u;
-                if (l == l0 + 4u)
-                    for (uint32_t j = l0 + 4u; j < t.maxlen; ++j) l += w64 > t.lim_incl[j] ? 1u : 0u;
-                const uint64_t off = (w64 >> (64u - l)) - t.first_code[l];
-                if (off < (uint64_t)t.count[l]) {
-                    e = (l << 8) | t.sorted[(t.base[l] + (uint32_t)off) & 255u];
-                } else {          // no codeword starts here
-                    bad = true;
-                    e = 1u << 8;
+        for (int q = 0; q < DE_GROUP / DE_REFILL; ++q) {
+            win = ls.window64(mw = m);
+            uint32_t any = 0u, es[DE_REFILL];
+#pragma unroll
+            for (int b = 0; b < DE_REFILL; ++b) {
+                uint32_t e = t.lut[(uint32_t)(win >> 32) >> shift];
+                uint32_t drop = e >> 8;
+                if (LONG && !AGAIN && drop == DE_MISS_LEN) {   // skipped by the wavefront when no lane is here
+                    e = search(ls.window64(m));
+                    drop = 0u;
+                    mw = m - (e >> 8);
+                    win = ls.window64(mw);
+                }
+                es[b] = e;
+                any |= e;
+                m -= e >> 8;
+                win <<= drop & 63u;
+                w[q] = __builtin_amdgcn_alignbit(e, w[q], 8);
+            }
+            if (AGAIN && (any & 0x8000u) != 0u) {      // of all lengths only that of a miss has its top bit set
+                m = mw;
+                int b = 0;                             // the first miss: what stands before it is right
+#pragma unroll
+                for (int k = 0; k < DE_REFILL - 1; ++k)
+                    if (b == k && (es[k] & 0x8000u) == 0u) {
+                        m -= es[k] >> 8;
+                        b = k + 1;
+                    }
+                uint32_t e = DE_MISS_LEN << 8;
+                win = ls.window64(mw = m);
+#pragma unroll 1
+                for (;;) {
+                    if ((e >> 8) == DE_MISS_LEN) {
+                        e = search(win);
+                        win = ls.window64(mw = m - (e >> 8));
+                    } else {
+                        win <<= (e >> 8) & 63u;
+                    }
+                    m -= e >> 8;
+                    w[q] = (w[q] & ~(0xffu << (8 * b))) | ((e & 0xffu) << (8 * b));
+                    if (++b == DE_REFILL) break;
+                    e = t.lut[(uint32_t)(win >> 32) >> shift];
                 }
             }
-            m -= e >> 8;
-            w[b >> 2] = __builtin_amdgcn_alignbit(e, w[b >> 2], 8);
         }
         }
         ls.rel = 0u - m;
-        // every window read above (up to three dwords from the current one) must have been resident
-        if (MODE == DE_LONG    ? (bad || ls.rel + 96u > ls.loaded * 128u)
-            : MODE == DE_PAIRS ? (bad || ls.rel + 64u > ls.loaded * 128u)
-                               : (ls.rel - rel0 > DE_GROUP * Tables::kBits ||
-                                  ls.rel + 64u > ls.loaded * 128u)) {   // rare
+        // every window read above (96 bits from the last one's position on) must have been resident
+        if (bad || 96u - mw > ls.loaded * 128u ||
+            (MODE == DE_SHORT && ls.rel - rel0 > DE_GROUP * Tables::kBits)) {   // rare
             ls.rel = rel0;
             decode_run_careful(t, ls, shift, DE_GROUP, ok, w);
         }
@@ -451,19 +535,17 @@ __device__ __forceinline__ void decode_chunk_packed(const DecTables &t, LaneStre
         ls.group_boundary();
         const uint32_t rel0 = ls.rel;
         uint32_t w[4] = {0u, 0u, 0u, 0u};
-        uint32_t m = 0u - rel0;
+        uint32_t m = 0u - rel0, mw = m;
+        uint64_t win = 0;
         bool bad = false;
 #pragma unroll
         for (int b = 0; b < DE_GROUP; ++b) {
-            const uint32_t *pc = ls.slot + ((m >> 5) & 15u) * RING_ROW_DW;
-            const uint32_t win = __builtin_amdgcn_alignbit(pc[RING_ROW_DW], pc[0], m);
-            uint32_t e = pairs[win >> (32 - DE_PAIR_BITS)];
-            if ((e >> 24) == 0u) e = pair_second<true>(ls, pairs, e, m, bad);   // rare
-            m -= e >> 24;
+            if (b % DE_REFILL == 0) win = ls.window64(mw = m);
+            const uint32_t e = pair_step<true>(ls, pairs, win, m, mw, bad);
             w[b >> 2] = __builtin_amdgcn_alignbit(e, w[b >> 2], 8);
         }
         ls.rel = 0u - m;
-        if (bad || ls.rel + 64u > ls.loaded * 128u) {   // rare: see decode_range
+        if (bad || 96u - mw > ls.loaded * 128u) {   // rare: see decode_range
             ls.rel = rel0;
             careful(2 * DE_GROUP, w);
         }
@@ -485,7 +567,7 @@ __device__ __forceinline__ void decode_chunk_packed(const DecTables &t, LaneStre
 template <bool TILED, bool PAIRS>
 __global__ __launch_bounds__(DE_BLOCK) void k_decode(const uint64_t *__restrict__ words, int64_t cap_words,
                                                       const uint64_t *__restrict__ chunk_bitoff, int chunk_syms,
-                                                      int64_t nchunks, const void *__restrict__ codes,
+                                                      int64_t nchunks, int chunks_per_block, const void *__restrict__ codes,
                                                       int code_per_user, int64_t n, uint8_t *__restrict__ sym_out,
                                                       int64_t stride, int32_t *status)
 {
@@ -494,16 +576,15 @@ __global__ __launch_bounds__(DE_BLOCK) void k_decode(const uint64_t *__restrict_
     __shared__ struct {
         uint32_t pairs[PAIRS ? (1 << DE_PAIR_BITS) : 1];
         DecTablesT<PAIRS ? CO3_LUT_BITS_MAX : DE_WIDE_BITS> t;   // one symbol per lookup: the widened table
-        alignas(256) uint32_t ring[DE_BLOCK * RING_ROWS];   // a multiple of the ring row: row offsets stay immediates
     } lds;
+    extern __shared__ __align__(256) uint32_t ring[];   // chunks_per_block * RING_ROWS
     auto &t = lds.t;
-    uint32_t *const ring = lds.ring;
     uint32_t *const pairs = lds.pairs;
 
     // The chunk's stream position and its first blocks are requested before the tables are loaded, so
     // that the three memory latencies at the start of a workgroup overlap.
-    const int64_t c = (int64_t)blockIdx.x * DE_BLOCK + threadIdx.x;
-    const bool active = c < nchunks;
+    const int64_t c = (int64_t)blockIdx.x * chunks_per_block + threadIdx.x;
+    const bool active = (int)threadIdx.x < chunks_per_block && c < nchunks;   // further wavefronts load tables only
     const uint64_t *off = chunk_bitoff + (int64_t)u * (nchunks + 1);
     const uint64_t p0 = active ? off[c] : 0, p1 = active ? off[c + 1] : 0;
     LaneStream ls;
@@ -766,6 +847,22 @@ __global__ __launch_bounds__(PT_WAVES(NIB) * CO3_WAVE) void k_ps_sum_tiled(const
     }
 }
 
+// Chunks (lanes) per workgroup of k_decode.  A chip that the chunks do not fill: as few wavefronts a workgroup as
+// spread them over all compute units (the lookups of the wavefronts of one unit share its LDS).  A full chip:
+// eight, so that two workgroups share a unit and one loads its tables while the other decodes; us with 8 | 16
+// wavefronts: 16 x 25 M E4M3 324 | 349, 10 x 11.2 M E4M3 118 | 126, 1 x 100 M E5M2 91 | 99, 10 x 11.2 M E3M0 48.4 | 49.3
+// (ten wavefronts 325, 125, 108, 52; twelve 350, 131, 92, 54).
+static int decode_chunks_per_block(int64_t nchunks, int U)
+{
+    int dev = 0, cus = 0;
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1)
+        cus = 256;
+    const int64_t waves = (nchunks + CO3_WAVE - 1) / CO3_WAVE * U;
+    const int64_t w = (waves + cus - 1) / cus;
+    return (int)(w < 1 ? 1 : w > DE_BLOCK / CO3_WAVE ? DE_BLOCK / CO3_WAVE : w) * CO3_WAVE;
+}
+
 // seg_off != NULL selects one code per tensor (codes[tensor], shared by the users) instead of codes[user]
 hipError_t co3_launch_decode(const uint64_t *words, int64_t cap_words, const uint64_t *chunk_bitoff, int chunk_syms,
                              const void *codes, const int64_t *seg_off, int nseg, int K, int64_t n, int U,
@@ -773,11 +870,13 @@ hipError_t co3_launch_decode(const uint64_t *words, int64_t cap_words, const uin
 {
     const int64_t nchunks = (n + chunk_syms - 1) / chunk_syms;
     if (nchunks <= 0) return hipSuccess;
-    unsigned blocks = (unsigned)((nchunks + DE_BLOCK - 1) / DE_BLOCK);
+    const int per_block = decode_chunks_per_block(nchunks, U);
+    const unsigned blocks = (unsigned)((nchunks + per_block - 1) / per_block);
     const unsigned lblocks = (unsigned)((nchunks + DL_BLOCK - 1) / DL_BLOCK);
 #define CO3_DECODE_LAUNCH(T, P)                                                                                    \
-    hipLaunchKernelGGL((k_decode<T, P>), dim3(blocks, U), dim3(DE_BLOCK), 0, st, words, cap_words, chunk_bitoff,   \
-                       chunk_syms, nchunks, codes, code_per_user, n, sym_out, stride, status)
+    hipLaunchKernelGGL((k_decode<T, P>), dim3(blocks, U), dim3(per_block < DE_MIN_BLOCK ? DE_MIN_BLOCK : per_block), \
+                       (size_t)per_block * RING_ROWS * sizeof(uint32_t), st, words, cap_words, chunk_bitoff, chunk_syms, \
+                       nchunks, per_block, codes, code_per_user, n, sym_out, stride, status)
     Co3LaunchTimer tm(CO3_K_DECODE, st);
     // one code for everything, shared by the users: the per-user kernels with every user reading codes[0]
     const int code_per_user = seg_off == nullptr;
