@@ -717,7 +717,9 @@ __global__ __launch_bounds__(DL_BLOCK) void k_decode_layers(const uint64_t *__re
 // TABLE != 0 (one tensor, i.e. one anchor per user): the values of every user's symbols are computed
 // once per block into LDS, and an element costs one LDS read and one add.  TABLE = 1 keeps all K
 // values; TABLE = 2 (larger alphabets) keeps the K/2 magnitudes and applies the sign bit after the
-// read, halving the LDS footprint.
+// read, halving the LDS footprint.  TABLE = 3 (several tensors): a step whose elements lie in one tensor takes
+// its K/2 magnitudes of every user from LDS as TABLE = 2 does (U * K/2 values computed for 4096 * U symbols;
+// 10 users of 11.2 M elements in 62 tensors, E4M3: 90 -> 69 us); the other steps look up a tensor per run or element.
 template <int TABLE, bool NIB>
 __global__ __launch_bounds__(PT_WAVES(NIB) * CO3_WAVE) void k_ps_sum_tiled(const uint8_t *__restrict__ symt, int64_t n, int U,
                                                             int64_t ws_stride, int chunk_syms, int64_t nruns,
@@ -745,10 +747,12 @@ __global__ __launch_bounds__(PT_WAVES(NIB) * CO3_WAVE) void k_ps_sum_tiled(const
     auto symbol = [&](const uint32_t (&w)[4], int k) -> uint32_t {
         return NIB ? (w[k >> 3] >> (4 * (k & 7))) & 0xfu : (w[k >> 2] >> (8 * (k & 3))) & 0xffu;
     };
-    __shared__ int64_t seg_cache[TABLE ? 1 : CO3_SEG_CACHE];     // TABLE: one tensor, nothing to look up
-    const int64_t *seg_off = TABLE ? seg_off_g : co3_cache_segs(seg_off_g, nseg, seg_cache);
+    constexpr bool ONE = TABLE == 1 || TABLE == 2;               // one tensor, nothing to look up
+    __shared__ int64_t seg_cache[ONE ? 1 : CO3_SEG_CACHE];
+    const int64_t *seg_off = ONE ? seg_off_g : co3_cache_segs(seg_off_g, nseg, seg_cache);
     extern __shared__ float value_of[];    // [U][K] or [U][K/2], TABLE only
-    if (TABLE) {
+    int table_seg = -1;                    // TABLE 3: the tensor whose values are there
+    if (ONE) {
         const int H = TABLE == 1 ? fc.K : fc.K >> 1;
         for (int j = threadIdx.x; j < U * H; j += PT_BLOCK) {
             const int u = j / H;
@@ -791,11 +795,28 @@ __global__ __launch_bounds__(PT_WAVES(NIB) * CO3_WAVE) void k_ps_sum_tiled(const
             }
         }
         const int64_t i_first = i0 < n ? i0 : n - 1;       // lanes past the end compute on the last element's
-        const int s_lo = TABLE ? 0 : co3_find_seg(seg_off, nseg, i_first);   // tensor and store nothing
+        const int s_lo = ONE ? 0 : co3_find_seg(seg_off, nseg, i_first);   // tensor and store nothing
         const int64_t i_last = i0 + EPT - 1 < n ? i0 + EPT - 1 : n - 1;
-        const int s_hi = TABLE ? 0 : co3_find_seg(seg_off, nseg, i_last);
+        const int s_hi = ONE ? 0 : co3_find_seg(seg_off, nseg, i_last);
+        bool from_table = ONE;
+        if (TABLE == 3) {
+            // the elements of the whole step lie between those of its first and last lane
+            const int64_t b0 = tile * CO3_WAVE * chunk_syms + (int64_t)(run - wr) * EPT;
+            const int64_t b1 = b0 + (int64_t)(CO3_WAVE - 1) * chunk_syms + ROW - 1;
+            const int bs = co3_find_seg(seg_off, nseg, b0 < n ? b0 : n - 1);
+            from_table = bs == co3_find_seg(seg_off, nseg, b1 < n ? b1 : n - 1);     // the same for all threads
+            if (from_table && bs != table_seg) {       // (every read of the last values lies before a barrier below)
+                const int H = fc.K >> 1;
+                for (int j = threadIdx.x; j < U * H; j += PT_BLOCK) {
+                    const int u = j / H;
+                    value_of[j] = value((uint32_t)(j - u * H), u, bs);
+                }
+                table_seg = bs;
+                __syncthreads();
+            }
+        }
         if (i0 >= n) {
-        } else if (TABLE) {
+        } else if (from_table) {
             for (int u = 0; u < U; ++u) {
                 const float *vu = value_of + u * (TABLE == 1 ? fc.K : fc.K >> 1);
                 uint4 v = ld_stream_u4(src + (int64_t)u * ws_stride);
@@ -804,7 +825,8 @@ __global__ __launch_bounds__(PT_WAVES(NIB) * CO3_WAVE) void k_ps_sum_tiled(const
                 for (int k = 0; k < EPT; ++k) {
                     const uint32_t sy = symbol(w, k);
                     if (TABLE == 1) acc[k] += vu[sy & ((uint32_t)fc.K - 1u)];
-                    else acc[k] += __uint_as_float(__float_as_uint(vu[sy & cmask]) | (((sy >> EM) & 1u) << 31));
+                    else if (TABLE == 2) acc[k] += __uint_as_float(__float_as_uint(vu[sy & cmask]) | (((sy >> EM) & 1u) << 31));
+                    else acc[k] += __uint_as_float(__float_as_uint(vu[sy & cmask]) ^ (((sy >> EM) & 1u) << 31));
                 }
             }
         } else if (s_lo == s_hi) {
@@ -822,14 +844,18 @@ __global__ __launch_bounds__(PT_WAVES(NIB) * CO3_WAVE) void k_ps_sum_tiled(const
                 }
             }
         } else {                           // the run straddles tensors: anchor per element
+            int seg_of[EPT];               // looked up once, not for every user
+            int sg = s_lo;
+#pragma unroll
+            for (int k = 0; k < EPT; ++k) {
+                while (sg < s_hi && seg_off[sg + 1] <= i0 + k) ++sg;
+                seg_of[k] = sg;
+            }
             for (int u = 0; u < U; ++u) {
                 uint4 v = *reinterpret_cast<const uint4 *>(src + (int64_t)u * ws_stride);
                 uint32_t w[4] = {v.x, v.y, v.z, v.w};
 #pragma unroll
-                for (int k = 0; k < EPT; ++k) {
-                    int sg = co3_find_seg(seg_off, nseg, i0 + k < n ? i0 + k : n - 1);
-                    acc[k] += value(symbol(w, k), u, sg);
-                }
+                for (int k = 0; k < EPT; ++k) acc[k] += value(symbol(w, k), u, seg_of[k]);
             }
         }
 #pragma unroll
@@ -912,14 +938,19 @@ hipError_t co3_launch_ps_sum_tiled(const uint8_t *symt, int64_t n, int U, int64_
     unsigned blocks = (unsigned)(b < 16384 ? b : 16384);
     Co3LaunchTimer tm(CO3_K_PS_SUM, st);
     const size_t full_bytes = (size_t)U * (size_t)(1 << (1 + fmt.exp_bits + fmt.mant_bits)) * sizeof(float);
+    // Several tensors: the values in LDS pay from three users on (11.2 M elements in 62 tensors, E4M3, us with |
+    // without: one user 25.2 | 21.5, four 37.3 | 42.0, ten 68.7 | 90.3).
+    const bool tables_pay = nseg > 1 && U >= 3;
 #define CO3_SUM_LAUNCH(T, P, BYTES)                                                                                \
     hipLaunchKernelGGL((k_ps_sum_tiled<T, P>), dim3(blocks), dim3(threads), BYTES, st, symt, n, U, ws_stride,     \
                        chunk_syms, nruns, anchor, scale, seg_off, nseg, fmt, acc_in, divisor, avg_out)
     if (packed) {       // alphabets of at most 16 symbols: the full table is 64 bytes per user
         if (nseg == 1 && full_bytes <= 4096) CO3_SUM_LAUNCH(1, true, full_bytes);
+        else if (tables_pay && full_bytes / 2 <= 32768) CO3_SUM_LAUNCH(3, true, full_bytes / 2);
         else CO3_SUM_LAUNCH(0, true, 0);
     } else if (nseg == 1 && full_bytes <= 4096) CO3_SUM_LAUNCH(1, false, full_bytes);
     else if (nseg == 1 && full_bytes / 2 <= 32768) CO3_SUM_LAUNCH(2, false, full_bytes / 2);
+    else if (tables_pay && full_bytes / 2 <= 32768) CO3_SUM_LAUNCH(3, false, full_bytes / 2);
     else CO3_SUM_LAUNCH(0, false, 0);
 #undef CO3_SUM_LAUNCH
     return hipGetLastError();

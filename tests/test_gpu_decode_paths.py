@@ -1,7 +1,11 @@
 """The decoder's registers-held window and its workgroup sizes: stretches of codewords beyond the table in runs
-that otherwise hit it, at one to eight wavefronts a workgroup.  Everything is defined bit for bit."""
+that otherwise hit it, at one to eight wavefronts a workgroup, and the average with the values of a tensor in LDS
+against an anchor per run or element.  Everything is defined bit for bit."""
 import numpy as np
 import pytest
+
+import oracle
+import co3_inputs as inp
 
 pytestmark = pytest.mark.gpu
 
@@ -40,3 +44,32 @@ def test_stretches_of_long_codewords(co3, E, M, n, C, U):
     assert pipe.poll() == 0
     assert torch.equal(pipe.sym_dec[:, :n], s)
 
+
+LAYOUTS = {
+    "one tile and less": [5000, 3, 0, 900],
+    "steps inside tensors": [100_000, 60_001, 7],
+    "tile edges": [16_384, 16_384, 1, 16_383, 64],
+    "many small": [37] * 700 + [40_000] + [1] * 65,
+}
+
+
+@pytest.mark.parametrize("layout", list(LAYOUTS))
+@pytest.mark.parametrize("E,M", [(3, 0), (3, 1), (4, 3)])
+@pytest.mark.parametrize("U", [1, 2, 3, 5])
+def test_average_of_several_tensors(co3, layout, E, M, U):
+    sizes = LAYOUTS[layout]
+    seg = inp.seg_offsets(sizes)
+    n = int(seg[-1])
+    fmt, f = co3.Fmt(E, M), oracle.Fmt(E, M)
+    r = np.random.default_rng(U * 7 + E)
+    scale = np.repeat(10.0 ** r.uniform(-30, 20, len(sizes)), sizes)
+    g = (r.standard_normal((U, n)) * scale).astype(np.float32)
+    pipe = co3.Co3Pipeline(U, n, fmt, seg_off=seg)
+    buf = pipe.new_gradient_buffer()
+    buf[:, :n] = torch.from_numpy(g).cuda()
+    pipe.step(buf)
+    assert pipe.poll() == 0
+    A = np.stack([oracle.anchor(g[u], f, seg) for u in range(U)])
+    sym = np.stack([oracle.convert_ef(g[u], np.zeros(n, np.float32), A[u], 1.0, f, seg)[0] for u in range(U)])
+    want = oracle.aggregate(sym, A, f, seg)
+    assert np.array_equal(pipe.avg[:n].cpu().numpy().view(np.uint32), want.view(np.uint32))
