@@ -412,12 +412,18 @@ __device__ __forceinline__ void stage_bits(unsigned long long *stage, int64_t wi
 // The per-user form is compiled for eight wavefronts per SIMD (64 registers; a few spills on the rarely taken
 // paths): the kernel is bound by the latency of its per-tile chain, and residency is what hides it (C3:
 // 61 -> 55 us against six wavefronts per SIMD).
-template <bool LAYERS>
+//
+// SCAN: groupoff holds the sizes of at most 64 groups as the sizes pass left them.  Every wavefront takes them with
+// one load, beside those it makes anyway, and scans them in registers; the first one of a user writes what the
+// scan kernel would.  That saves the kernel (3.3 us and its place in a chain of small ones: one user of 65,536
+// elements 53.9 -> 50.0 us a pass).  With up to 682 groups a form of this took 59 us against 51 and the kernel's 5.
+template <bool LAYERS, bool SCAN>
 __global__ __launch_bounds__(EN_BLOCK) __attribute__((amdgpu_waves_per_eu(LAYERS ? 5 : 8, LAYERS ? 5 : 8)))
 void k_enc_pack(const uint8_t *__restrict__ sym, int64_t n, int64_t stride, const void *__restrict__ codes, int K,
                 const int64_t *__restrict__ seg_off_g, int nseg, const uint64_t *__restrict__ tileoff, int64_t nblk,
                 const uint64_t *__restrict__ groupoff, int64_t ngrp, uint64_t *__restrict__ words, int64_t cap_words,
-                int chunk_syms, uint64_t *__restrict__ chunk_bitoff, int64_t nchunks, int sym_nib)
+                int chunk_syms, uint64_t *__restrict__ chunk_bitoff, int64_t nchunks, int sym_nib,
+                uint64_t *__restrict__ total_bits, int32_t *status)
 {
     const int u = blockIdx.y;
     const bool nib = !LAYERS && sym_nib != 0;
@@ -449,7 +455,10 @@ void k_enc_pack(const uint8_t *__restrict__ sym, int64_t n, int64_t stride, cons
     const int64_t i2 = t1 + lane;
     const bool has_next = live && t1 > t0 && lane < CO3_WAVE - 1 && i2 < n;
     const uint32_t next_sym = has_next ? load_sym1(su, i2, nib) : 0u;
-    const uint64_t group_base = live ? groupoff[(int64_t)u * ngrp + tb / CO3_PACK_GROUP] : 0ull;
+    uint64_t group_base = 0;
+    uint32_t group_bits = 0;                         // SCAN: of group `lane`; 64 groups of codewords fit 32 bits
+    if (SCAN) group_bits = lane < (int)ngrp ? (uint32_t)groupoff[(int64_t)u * ngrp + lane] : 0u;
+    else if (live) group_base = groupoff[(int64_t)u * ngrp + tb / CO3_PACK_GROUP];
     const uint64_t tile_base = live ? tileoff[(int64_t)u * nblk + tb] : 0ull;
 
     const uint64_t *enc_s = LAYERS ? enc_all + wave * 256 : enc_all;
@@ -470,6 +479,16 @@ void k_enc_pack(const uint8_t *__restrict__ sym, int64_t n, int64_t stride, cons
         maxlen = cd->maxlen;
         __syncthreads();
         if (tb >= nblk) return;
+        if (SCAN) {
+            const uint32_t upto = wave_scan_incl_u32(group_bits, lane);
+            const int grp = __builtin_amdgcn_readfirstlane((int)(tb / CO3_PACK_GROUP));
+            group_base = grp ? (uint32_t)__builtin_amdgcn_readlane((int)upto, grp - 1) : 0u;
+            if (tb == 0 && lane == CO3_WAVE - 1) {   // the last lane holds the stream's length
+                total_bits[u] = upto;
+                chunk_bitoff[(int64_t)u * (nchunks + 1) + nchunks] = upto;
+                if (((uint64_t)upto + 63) / 64 > (uint64_t)cap_words) co3_raise(status, CO3_ECAP);
+            }
+        }
     } else {
         seg_off = co3_cache_segs(seg_off_g, nseg, seg_cache);
         __syncthreads();
@@ -666,19 +685,25 @@ hipError_t co3_launch_encode(const uint8_t *sym, int64_t n, int U, int64_t strid
             hipLaunchKernelGGL(k_enc_sizes, dim3((unsigned)ngrp, U), dim3(EN_BLOCK), 0, st, sym, n, stride, codes, K,
                                tilesum, nblk, groupsum, ngrp, status, sym_nib);
     }
-    if (co3_launch_enc_scan(groupsum, ngrp, U, cap_words, chunk_bitoff, nchunks, total_bits, status, st) != hipSuccess)
+    static_assert((int64_t)CO3_WAVE * CO3_PACK_GROUP * CO3_PACK_SYMS * 64 < (1ll << 32), "64 groups fit 32 bits");
+    const bool scan_in_pack = !seg_off && nblk > 0 && ngrp <= CO3_WAVE;
+    if (!scan_in_pack && co3_launch_enc_scan(groupsum, ngrp, U, cap_words, chunk_bitoff, nchunks, total_bits, status, st) != hipSuccess)
         return hipGetLastError();
     if (nblk > 0) {
         const unsigned gx = (unsigned)((nblk + EN_WAVES - 1) / EN_WAVES);
         Co3LaunchTimer tm(CO3_K_ENC_PACK, st);
         if (seg_off)
-            hipLaunchKernelGGL(k_enc_pack<true>, dim3(gx, U), dim3(EN_BLOCK), 0, st, sym, n, stride, codes, K, seg_off,
+            hipLaunchKernelGGL((k_enc_pack<true, false>), dim3(gx, U), dim3(EN_BLOCK), 0, st, sym, n, stride, codes, K, seg_off,
                                nseg, (const uint64_t *)tilesum, nblk, (const uint64_t *)groupsum, ngrp, words,
-                               cap_words, chunk_syms, chunk_bitoff, nchunks, 0);
+                               cap_words, chunk_syms, chunk_bitoff, nchunks, 0, total_bits, status);
+        else if (scan_in_pack)
+            hipLaunchKernelGGL((k_enc_pack<false, true>), dim3(gx, U), dim3(EN_BLOCK), 0, st, sym, n, stride, codes, K, seg_off,
+                               nseg, (const uint64_t *)tilesum, nblk, (const uint64_t *)groupsum, ngrp, words,
+                               cap_words, chunk_syms, chunk_bitoff, nchunks, sym_nib, total_bits, status);
         else
-            hipLaunchKernelGGL(k_enc_pack<false>, dim3(gx, U), dim3(EN_BLOCK), 0, st, sym, n, stride, codes, K, seg_off,
+            hipLaunchKernelGGL((k_enc_pack<false, false>), dim3(gx, U), dim3(EN_BLOCK), 0, st, sym, n, stride, codes, K, seg_off,
                                nseg, (const uint64_t *)tilesum, nblk, (const uint64_t *)groupsum, ngrp, words,
-                               cap_words, chunk_syms, chunk_bitoff, nchunks, sym_nib);
+                               cap_words, chunk_syms, chunk_bitoff, nchunks, sym_nib, total_bits, status);
     }
     return hipGetLastError();
 }

@@ -73,3 +73,31 @@ def test_average_of_several_tensors(co3, layout, E, M, U):
     sym = np.stack([oracle.convert_ef(g[u], np.zeros(n, np.float32), A[u], 1.0, f, seg)[0] for u in range(U)])
     want = oracle.aggregate(sym, A, f, seg)
     assert np.array_equal(pipe.avg[:n].cpu().numpy().view(np.uint32), want.view(np.uint32))
+
+
+@pytest.mark.parametrize("E,M", [(3, 0), (4, 3)])
+@pytest.mark.parametrize("n", [1, 1024, 16_384, 16_385, 64 * 16_384 - 1, 64 * 16_384, 64 * 16_384 + 1])
+def test_group_offsets_in_the_packer(co3, n, E, M):
+    """Up to 64 groups of tiles the packer scans the group sizes itself; the stream, its index and its length are
+    the oracle's on both sides of the line, and a stream beyond its capacity is reported on both."""
+    fmt, f = co3.Fmt(E, M), oracle.Fmt(E, M)
+    g = (np.random.default_rng(n).standard_normal(n) * 1e-3).astype(np.float32)
+    A = oracle.anchor(g, f)
+    s, _ = oracle.convert_ef(g, np.zeros(n, np.float32), A, 1.0, f)
+    lengths = oracle.huffman_lengths(oracle.histogram(s, f))
+    words, off, total = oracle.encode(s, lengths, oracle.canonical_codes(lengths), 256)
+    need = (total + 63) // 64
+    need += need & 1
+    for cap, want in ((need, 0), (need - 2, co3.binding.ECAP)):
+        if cap == 0:
+            continue
+        pipe = co3.Co3Pipeline(1, n, fmt, cap_words=need)
+        pipe.convert(torch.nn.functional.pad(torch.from_numpy(g), (0, pipe.stride - n)).reshape(1, -1).cuda())
+        pipe.build()
+        w = torch.zeros((1, cap), dtype=torch.int64, device="cuda")
+        co3.binding.encode(pipe.sym, n, fmt, pipe.codes, w, 256, pipe.chunk_bitoff, pipe.total_bits, pipe.enc_ws, pipe.status)
+        assert pipe.poll() == want
+        assert int(pipe.total_bits[0].item()) == total
+        assert np.array_equal(pipe.chunk_bitoff[0].cpu().numpy().view(np.uint64), off)
+        if want == 0:
+            assert np.array_equal(w[0, :(total + 63) // 64].cpu().numpy().view(np.uint64), words[:(total + 63) // 64])
