@@ -28,7 +28,9 @@ __device__ __forceinline__ const Co3Code *dcode_of(const void *codes, int u)
 #define DE_GROUP 16          // symbols per run: one ring refill point, one 16-byte store
 #define DE_MISS_LEN 255u     // length field of a table entry that does not resolve a symbol
 #define DE_PAIR_BITS 12      // prefix length of the two-symbol table used for alphabets of at most 16 symbols
-#define DE_REFILL 4          // table lookups between two reads of the ring: 4 x 14 bits lie in a window of 64
+// Table lookups between two reads of the ring: 4 x 14 bits lie in a window of 64.  That holds for hits alone: a
+// codeword that the table does not resolve (up to CO3_MAX_CODE_LEN bits) is searched in a window read at its start.
+#define DE_REFILL 4
 enum { DE_SHORT = 0, DE_LONG = 1, DE_PAIRS = 2 };   // fast-path variants of decode_range
 
 struct LaneStream {
@@ -479,11 +481,10 @@ __device__ __forceinline__ void decode_range(const Tables &t, LaneStream &ls, in
                         b = k + 1;
                     }
                 uint32_t e = DE_MISS_LEN << 8;
-                win = ls.window64(mw = m);
 #pragma unroll 1
                 for (;;) {
-                    if ((e >> 8) == DE_MISS_LEN) {
-                        e = search(win);
+                    if ((e >> 8) == DE_MISS_LEN) {     // (hits since the last read have left win short of bits)
+                        e = search(ls.window64(m));
                         win = ls.window64(mw = m - (e >> 8));
                     } else {
                         win <<= (e >> 8) & 63u;

@@ -45,6 +45,54 @@ def test_stretches_of_long_codewords(co3, E, M, n, C, U):
     assert torch.equal(pipe.sym_dec[:, :n], s)
 
 
+def fibonacci(k):
+    w = [1, 1]
+    while len(w) < k:
+        w.append(w[-1] + w[-2])
+    return w[:k]
+
+
+# codes whose longest codewords (43 and 52 bits) do not fit what a window of 64 bits holds after two hits of the
+# 14-bit table (36 bits), the second one not even what it holds after one (50)
+DEEP = {"43 bits": fibonacci(44), "52 bits": fibonacci(47) + [2**32 - 1] * 200}
+
+
+def runs_around_misses(lengths):
+    """Runs of 16 symbols: every group of four drawn from the longest codeword, two that the table misses, two hits
+    at and below its width and the shortest, at each of the run's four places, shortest codewords around it."""
+    by_length = [int(np.flatnonzero(lengths == k)[-1]) for k in (lengths.max(), 37, 20, 14, 13, lengths[lengths > 0].min())]
+    groups = np.stack(np.meshgrid(*[by_length] * 4, indexing="ij"), axis=-1).reshape(-1, 4)
+    runs = np.full((len(groups), 4, 16), by_length[-1], np.uint8)
+    for q in range(4):
+        runs[:, q, 4 * q:4 * q + 4] = groups
+    return runs.reshape(-1)
+
+
+@pytest.mark.parametrize("C", [64, 256])
+@pytest.mark.parametrize("code", list(DEEP))
+def test_misses_around_hits(co3, code, C):
+    fmt, f = co3.Fmt(4, 3), oracle.Fmt(4, 3)
+    w = np.zeros(256, np.uint32)
+    w[:len(DEEP[code])] = DEEP[code]
+    lengths = np.asarray(oracle.huffman_lengths(w))
+    s = runs_around_misses(lengths)
+    n, U = len(s), 2
+    words, off, total = oracle.encode(s, lengths, oracle.canonical_codes(lengths), C)
+    pipe = co3.Co3Pipeline(U, n, fmt, chunk_syms=C, cap_words=len(words) + 2)
+    pipe.sym[:, :n] = torch.from_numpy(s).cuda()
+    pipe.build(torch.from_numpy(np.tile(w.view(np.int32), (U, 1))).cuda())
+    pipe.encode()
+    assert np.array_equal(pipe.words[1, :(total + 63) // 64].cpu().numpy().view(np.uint64), words[:(total + 63) // 64])
+    pipe.decode()
+    got = pipe.sym_dec[:, :n].cpu().numpy()
+    assert np.array_equal(got, np.tile(s, (U, 1)))
+    pipe.anchor[:] = torch.tensor([[3], [-2]], dtype=torch.int32)
+    pipe.aggregate()
+    want = oracle.aggregate(np.tile(s, (U, 1)), np.array([[3], [-2]], np.int32), f)
+    assert np.array_equal(pipe.avg[:n].cpu().numpy().view(np.uint32), want.view(np.uint32))
+    assert pipe.poll() == 0
+
+
 LAYOUTS = {
     "one tile and less": [5000, 3, 0, 900],
     "steps inside tensors": [100_000, 60_001, 7],
