@@ -193,8 +193,9 @@ __device__ __forceinline__ void load_tables(Tables &t, const Co3Code *cd)
             uint32_t e = ((k < 2u ? v[r].x : v[r].y) >> (16 * (k & 1))) & 0xffffu;
             if ((e >> 8) == 0u) e = DE_MISS_LEN << 8;                      // longer than the prefix, or invalid
             const uint32_t at = q * 4u + k;
+            if (at >= (1u << lb)) continue;                                // (a stored table of two entries)
             if (wide == 0u) {
-                if (at < (1u << lb)) t.lut[at] = (uint16_t)e;
+                t.lut[at] = (uint16_t)e;
             } else if (wide == 1u) {
                 reinterpret_cast<uint32_t *>(t.lut)[at] = e | (e << 16);
             } else {

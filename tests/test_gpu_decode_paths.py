@@ -93,6 +93,40 @@ def test_misses_around_hits(co3, code, C):
     assert pipe.poll() == 0
 
 
+@pytest.mark.parametrize("bits", [0, 1, 2, 3, 7, 11])
+@pytest.mark.parametrize("longest", [13, 14, 15, 19])
+def test_stored_table_of_a_shorter_prefix(co3, bits, longest):
+    """A code blob whose decoder table resolves fewer leading bits than the library's own (which takes 12; 0 is read
+    as 1): what it leaves out is entered from the canonical lengths, nothing is written beyond the widened table."""
+    fmt = co3.Fmt(4, 3)
+    w = np.zeros(256, np.uint32)
+    w[:longest + 1] = fibonacci(longest + 1)
+    lengths = np.asarray(oracle.huffman_lengths(w))
+    assert lengths.max() == longest
+    codewords = oracle.canonical_codes(lengths)
+    n = 64 * 256 + 5
+    s = np.random.default_rng(bits).integers(0, longest + 1, n).astype(np.uint8)
+    pipe = co3.Co3Pipeline(1, n, fmt, cap_words=n // 2)
+    pipe.sym[0, :n] = torch.from_numpy(s).cuda()
+    pipe.build(torch.from_numpy(w.view(np.int32)).cuda().reshape(1, 256))
+    pipe.encode()
+    assert pipe.poll() == 0
+    blob = pipe.codes[0].cpu().numpy().copy()
+    lut_bits = blob[3352:3356].view(np.uint32)       # behind len, enc, first_code, count, base, sorted, nact, maxlen
+    lut = blob[3360:3360 + 2 * 4096].view(np.uint16)
+    assert int(lut_bits[0]) == 12 and int(lut[0]) == (1 << 8 | longest)
+    stored = max(bits, 1)
+    lut[:] = 0
+    for k in np.flatnonzero((lengths > 0) & (lengths <= stored)):
+        span = 1 << (stored - int(lengths[k]))
+        lut[int(codewords[k]) * span:(int(codewords[k]) + 1) * span] = (int(lengths[k]) << 8) | k
+    lut_bits[0] = bits
+    pipe.codes[0] = torch.from_numpy(blob).cuda()
+    pipe.decode()
+    assert pipe.poll() == 0
+    assert np.array_equal(pipe.sym_dec[0, :n].cpu().numpy(), s)
+
+
 LAYOUTS = {
     "one tile and less": [5000, 3, 0, 900],
     "steps inside tensors": [100_000, 60_001, 7],
