@@ -31,7 +31,7 @@ __device__ __forceinline__ const Co3Code *dcode_of(const void *codes, int u)
 // Table lookups between two reads of the ring: 4 x 14 bits lie in a window of 64.  That holds for hits alone: a
 // codeword that the table does not resolve (up to CO3_MAX_CODE_LEN bits) is searched in a window read at its start.
 #define DE_REFILL 4
-enum { DE_SHORT = 0, DE_LONG = 1, DE_PAIRS = 2 };   // fast-path variants of decode_range
+enum { DE_SHORT = 0, DE_LONG = 1, DE_PAIRS = 2, DE_RETRY = 3 };   // fast-path variants of decode_range
 
 struct LaneStream {
     const uint4 *blocks;   // the user's stream as 16-byte blocks
@@ -349,9 +349,9 @@ __device__ __forceinline__ uint32_t pair_step(const LaneStream &ls, const uint32
 // The fast path decodes a run without a residency check per symbol and validates it afterwards:
 // every window it read must lie inside the blocks that were resident when the run started, and
 // every window must have started a codeword.  Otherwise the run is decoded again by the careful
-// path from the saved position.  Codewords longer than the table prefix are resolved in place by a
+// path from the saved position.  Codewords longer than the table prefix are resolved by a
 // canonical search (the lengths' upper limits are ordered), in a branch the wavefront skips when
-// no lane needs it.
+// no lane needs it: in place, symbol by symbol (DE_LONG), or after every four symbols (DE_RETRY).
 //
 // DE_SHORT is the instance for codes whose longest codeword fits the table prefix: there a miss can
 // only come from an invalid stream; it advances by DE_MISS_LEN, more than 16 hits can, which the
@@ -366,7 +366,7 @@ __device__ __forceinline__ void decode_range(const Tables &t, LaneStream &ls, in
 {
     static_assert(DE_REFILL * Tables::kBits <= 64 && DE_REFILL == 4, "a window holds the lookups between two refills");
     static_assert(DE_GROUP * Tables::kBits < DE_MISS_LEN, "a miss must advance more than a run of hits can");
-    constexpr bool LONG = MODE == DE_LONG;
+    constexpr bool AGAIN = MODE == DE_RETRY;
     const int shift = 32 - (int)t.lut_bits;
     int i = i0;
     // cnt < 16 symbols from symbol i on, inside one run
@@ -446,12 +446,12 @@ __device__ __forceinline__ void decode_range(const Tables &t, LaneStream &ls, in
             bad = true;                   // no codeword starts here
             return 1u << 8;
         };
-        // With the wide table a miss is rare (about one in 10^4 symbols of an 8-bit format): one test per
-        // DE_REFILL symbols, after which the lane goes on one by one from the first miss.  Against a test at every
-        // symbol, for which each lookup has to wait: 16 x 25 M E4M3 324 -> 305 us, 32 x 1 M E3M1 36 -> 28; one user's
-        // 62 tensors in E4M3, some with stretches of long codewords, 54 -> 60.  With the narrow table (one miss in
-        // 200 symbols) the codeword is searched in place.
-        constexpr bool AGAIN = LONG && Tables::kBits > CO3_LUT_BITS_MAX;
+        // DE_RETRY tests for misses once per DE_REFILL symbols, after which the lane goes on one by one from the
+        // first; DE_LONG tests at every symbol, and each lookup has to wait for the test of the last.  With the wide
+        // table a miss is rare in data that the code was made for (about one in 10^4 symbols of an 8-bit format):
+        // DE_LONG | DE_RETRY 16 x 25 M E4M3 423 | 408 us with the average, 32 x 1 M E3M1 60 | 52; but one user's 62
+        // tensors in E4M3, some with stretches of long codewords, 70 | 78.  With the narrow table (one miss in 200
+        // symbols) it is DE_LONG.
 #pragma unroll
         for (int q = 0; q < DE_GROUP / DE_REFILL; ++q) {
             win = ls.window64(mw = m);
@@ -460,7 +460,7 @@ __device__ __forceinline__ void decode_range(const Tables &t, LaneStream &ls, in
             for (int b = 0; b < DE_REFILL; ++b) {
                 uint32_t e = t.lut[(uint32_t)(win >> 32) >> shift];
                 uint32_t drop = e >> 8;
-                if (LONG && !AGAIN && drop == DE_MISS_LEN) {   // skipped by the wavefront when no lane is here
+                if (MODE == DE_LONG && drop == DE_MISS_LEN) {   // skipped by the wavefront when no lane is here
                     e = search(ls.window64(m));
                     drop = 0u;
                     mw = m - (e >> 8);
@@ -617,8 +617,13 @@ __global__ __launch_bounds__(DE_BLOCK) void k_decode(const uint64_t *__restrict_
     bool ok = true;
     if constexpr (PAIRS && TILED) decode_chunk_packed(t, ls, nsym, out, run_step, ok, pairs);
     else if constexpr (PAIRS) decode_range<DE_PAIRS>(t, ls, 0, nsym, out, run_step, ok, pairs);
-    else if (t.maxlen > t.lut_bits) decode_range<DE_LONG>(t, ls, 0, nsym, out, run_step, ok);
-    else decode_range<DE_SHORT>(t, ls, 0, nsym, out, run_step, ok);
+    // (More than eight bits a symbol: the code does not fit these symbols, and most of them lie beyond the table.
+    // Four users of 11.2 M in E4M3, 1 % | 20 % of them in stretches of 4,096 such: DE_LONG 789 | 803 us, DE_RETRY 839 |
+    // 838.  Matched data stay below 7.95 bits in chunks of 256; a line at 7.25 would serve one user's ResNet-18,
+    // 70 us for 78, and cost E4M3 of shape 0.5, at 7.19 bits by itself, 121 for 115.)
+    else if (t.maxlen <= t.lut_bits) decode_range<DE_SHORT>(t, ls, 0, nsym, out, run_step, ok);
+    else if (__any(p1 - p0 > (uint64_t)nsym * 8)) decode_range<DE_LONG>(t, ls, 0, nsym, out, run_step, ok);
+    else decode_range<DE_RETRY>(t, ls, 0, nsym, out, run_step, ok);
     ls.land();
     if (!(ok && ls.pos() == p1)) co3_raise(status, CO3_EBADSTREAM);
 }

@@ -57,27 +57,31 @@ def fibonacci(k):
 DEEP = {"43 bits": fibonacci(44), "52 bits": fibonacci(47) + [2**32 - 1] * 200}
 
 
-def runs_around_misses(lengths):
+def runs_around_misses(lengths, quiet):
     """Runs of 16 symbols: every group of four drawn from the longest codeword, two that the table misses, two hits
-    at and below its width and the shortest, at each of the run's four places, shortest codewords around it."""
+    at and below its width and the shortest, at each of the run's four places, shortest codewords around it and in
+    `quiet` further runs."""
     by_length = [int(np.flatnonzero(lengths == k)[-1]) for k in (lengths.max(), 37, 20, 14, 13, lengths[lengths > 0].min())]
     groups = np.stack(np.meshgrid(*[by_length] * 4, indexing="ij"), axis=-1).reshape(-1, 4)
-    runs = np.full((len(groups), 4, 16), by_length[-1], np.uint8)
+    runs = np.full((len(groups), 4, 16 * (1 + quiet)), by_length[-1], np.uint8)
     for q in range(4):
         runs[:, q, 4 * q:4 * q + 4] = groups
     return runs.reshape(-1)
 
 
-@pytest.mark.parametrize("C", [64, 256])
-@pytest.mark.parametrize("code", list(DEEP))
-def test_misses_around_hits(co3, code, C):
+# without quiet runs some chunks take more than eight bits a symbol, where the decoder tests for misses symbol by
+# symbol; with these no chunk does, and it tests after every four
+@pytest.mark.parametrize("code,C,quiet", [("43 bits", 64, 0), ("43 bits", 64, 1), ("43 bits", 256, 0), ("43 bits", 256, 3),
+                                          ("52 bits", 64, 0), ("52 bits", 256, 15)])
+def test_misses_around_hits(co3, code, C, quiet):
     fmt, f = co3.Fmt(4, 3), oracle.Fmt(4, 3)
     w = np.zeros(256, np.uint32)
     w[:len(DEEP[code])] = DEEP[code]
     lengths = np.asarray(oracle.huffman_lengths(w))
-    s = runs_around_misses(lengths)
+    s = runs_around_misses(lengths, quiet)
     n, U = len(s), 2
     words, off, total = oracle.encode(s, lengths, oracle.canonical_codes(lengths), C)
+    assert (int(np.diff(off.astype(np.int64)).max()) > 8 * C) == (quiet == 0)
     pipe = co3.Co3Pipeline(U, n, fmt, chunk_syms=C, cap_words=len(words) + 2)
     pipe.sym[:, :n] = torch.from_numpy(s).cuda()
     pipe.build(torch.from_numpy(np.tile(w.view(np.int32), (U, 1))).cuda())
