@@ -7,10 +7,7 @@
 #include <atomic>
 #include <vector>
 
-namespace {
-
-// ---- compute units of each device, looked up once -------------------------------------------
-int device_cus()
+int co3_device_cus()
 {
     static std::atomic<int> cus_of[64];
     int dev = -1;
@@ -22,6 +19,8 @@ int device_cus()
     }
     return c;
 }
+
+namespace {
 
 std::atomic<uint32_t> g_spin_limit{1u << 18};
 
@@ -304,7 +303,7 @@ void co3_set_exchange_spin_limit(int64_t polls)
 #endif
 static bool user_encode_coop(int64_t n, int32_t U, int32_t nseg, int *kpt, int *grid)
 {
-    const int cus = device_cus();
+    const int cus = co3_device_cus();
     if (nseg > 1 && U > CO3_COOP_SEGS_MAX_USERS) return false;
     return cus > 0 && co3_coop_fits(n, nseg, cus, kpt, grid);
 }

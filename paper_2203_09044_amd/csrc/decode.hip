@@ -619,8 +619,8 @@ __global__ __launch_bounds__(DE_BLOCK) void k_decode(const uint64_t *__restrict_
     else if constexpr (PAIRS) decode_range<DE_PAIRS>(t, ls, 0, nsym, out, run_step, ok, pairs);
     // (More than eight bits a symbol: the code does not fit these symbols, and most of them lie beyond the table.
     // Four users of 11.2 M in E4M3, 1 % | 20 % of them in stretches of 4,096 such: DE_LONG 789 | 803 us, DE_RETRY 839 |
-    // 838.  Matched data stay below 7.95 bits in chunks of 256; a line at 7.25 would serve one user's ResNet-18,
-    // 70 us for 78, and cost E4M3 of shape 0.5, at 7.19 bits by itself, 121 for 115.)
+    // 838.  Matched data stay below 7.7 bits in chunks of 256 and 8.2 of 64; a line at 7.25 would serve one user's
+    // ResNet-18, 70 us for 78, and cost E4M3 of shape 0.5, at 7.19 bits by itself, 121 for 115.)
     else if (t.maxlen <= t.lut_bits) decode_range<DE_SHORT>(t, ls, 0, nsym, out, run_step, ok);
     else if (__any(p1 - p0 > (uint64_t)nsym * 8)) decode_range<DE_LONG>(t, ls, 0, nsym, out, run_step, ok);
     else decode_range<DE_RETRY>(t, ls, 0, nsym, out, run_step, ok);
@@ -887,10 +887,7 @@ __global__ __launch_bounds__(PT_WAVES(NIB) * CO3_WAVE) void k_ps_sum_tiled(const
 // (ten wavefronts 325, 125, 108, 52; twelve 350, 131, 92, 54).
 static int decode_chunks_per_block(int64_t nchunks, int U)
 {
-    int dev = 0, cus = 0;
-    if (hipGetDevice(&dev) != hipSuccess ||
-        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1)
-        cus = 256;
+    const int known = co3_device_cus(), cus = known > 0 ? known : 256;
     const int64_t waves = (nchunks + CO3_WAVE - 1) / CO3_WAVE * U;
     const int64_t w = (waves + cus - 1) / cus;
     return (int)(w < 1 ? 1 : w > DE_BLOCK / CO3_WAVE ? DE_BLOCK / CO3_WAVE : w) * CO3_WAVE;

@@ -20,6 +20,9 @@ struct Co3LaunchTimer {
     hipStream_t stream;
 };
 
+// compute units of the current device (looked up once per device), 0 if they cannot be had
+int co3_device_cus();
+
 hipError_t co3_launch_fill(int32_t *a, int64_t na, int32_t va, uint32_t *b, int64_t nb, hipStream_t st, uint32_t vb = 0u);
 hipError_t co3_launch_absmax(const float *g, int64_t n, int U, int64_t stride, const int64_t *seg_off, int nseg,
                              int32_t *anchor, hipStream_t st);
