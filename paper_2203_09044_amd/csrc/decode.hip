@@ -726,15 +726,19 @@ __global__ __launch_bounds__(DL_BLOCK) void k_decode_layers(const uint64_t *__re
 // values; TABLE = 2 (larger alphabets) keeps the K/2 magnitudes and applies the sign bit after the
 // read, halving the LDS footprint.  TABLE = 3 (several tensors): a step whose elements lie in one tensor takes
 // its K/2 magnitudes of every user from LDS as TABLE = 2 does (U * K/2 values computed for 4096 * U symbols;
-// 10 users of 11.2 M elements in 62 tensors, E4M3: 90 -> 69 us); the other steps look up a tensor per run or element.
+// 16 users of 11.2 M elements in 62 tensors, E4M3: 113 -> 76 us); the other steps look up a tensor per run or element.
+//
+// Bound by latency and, with many users, by issue: how many wavefronts a SIMD holds counts.  They are set by the
+// runs that straddle tensors, though few do: with an address per element kept from user to user, and the 64-bit
+// comparisons that found its tensor, the kernel took 227 registers (NIB) and 132; now 128 and 82.  Average of
+// 11.2 M elements in 62 tensors, before | now: E3M0 two users 32 | 29 us, ten 70 | 55; E4M3 two 27 | 24, three
+// 36 | 28, ten 69 | 54.  In 33,333 tensors of three: E3M0 ten users 51 | 50.
 template <int TABLE, bool NIB>
-__global__ __launch_bounds__(PT_WAVES(NIB) * CO3_WAVE) void k_ps_sum_tiled(const uint8_t *__restrict__ symt, int64_t n, int U,
-                                                            int64_t ws_stride, int chunk_syms, int64_t nruns,
-                                                            const int32_t *__restrict__ anchor,
-                                                            const float *__restrict__ scale,
-                                                            const int64_t *__restrict__ seg_off_g, int nseg,
-                                                            co3_fmt fmt, const float *acc_in, float divisor,
-                                                            float *avg_out)
+__global__ __launch_bounds__(PT_WAVES(NIB) * CO3_WAVE) __attribute__((amdgpu_waves_per_eu(NIB ? 3 : 4)))
+void k_ps_sum_tiled(const uint8_t *__restrict__ symt, int64_t n, int U, int64_t ws_stride, int chunk_syms, int64_t nruns,
+                    const int32_t *__restrict__ anchor, const float *__restrict__ scale,
+                    const int64_t *__restrict__ seg_off_g, int nseg, co3_fmt fmt, const float *acc_in, float divisor,
+                    float *avg_out)
 {
     constexpr int EPT = NIB ? 32 : 16;     // elements per thread
     constexpr int WAVES = PT_WAVES(NIB), PT_BLOCK = WAVES * CO3_WAVE;
@@ -801,10 +805,6 @@ __global__ __launch_bounds__(PT_WAVES(NIB) * CO3_WAVE) void k_ps_sum_tiled(const
                     if (i0 + k < n) acc[k] = acc_in[i0 + k];
             }
         }
-        const int64_t i_first = i0 < n ? i0 : n - 1;       // lanes past the end compute on the last element's
-        const int s_lo = ONE ? 0 : co3_find_seg(seg_off, nseg, i_first);   // tensor and store nothing
-        const int64_t i_last = i0 + EPT - 1 < n ? i0 + EPT - 1 : n - 1;
-        const int s_hi = ONE ? 0 : co3_find_seg(seg_off, nseg, i_last);
         bool from_table = ONE;
         if (TABLE == 3) {
             // the elements of the whole step lie between those of its first and last lane
@@ -821,6 +821,11 @@ __global__ __launch_bounds__(PT_WAVES(NIB) * CO3_WAVE) void k_ps_sum_tiled(const
                 table_seg = bs;
                 __syncthreads();
             }
+        }
+        int s_lo = 0, s_hi = 0;                // first and last tensor of the run
+        if (!from_table) {
+            s_lo = co3_find_seg(seg_off, nseg, i0 < n ? i0 : n - 1);       // (lanes past the end store nothing)
+            s_hi = co3_find_seg(seg_off, nseg, i0 + EPT - 1 < n ? i0 + EPT - 1 : n - 1);
         }
         if (i0 >= n) {
         } else if (from_table) {
@@ -851,18 +856,30 @@ __global__ __launch_bounds__(PT_WAVES(NIB) * CO3_WAVE) void k_ps_sum_tiled(const
                 }
             }
         } else {                           // the run straddles tensors: anchor per element
-            int seg_of[EPT];               // looked up once, not for every user
-            int sg = s_lo;
+            uint32_t seg_of[EPT];          // looked up once, not for every user
+            uint32_t sg = (uint32_t)s_lo;
+            int next = s_lo < s_hi ? (int)(seg_off[sg + 1] - i0) : EPT;        // where the tensor after sg begins
 #pragma unroll
             for (int k = 0; k < EPT; ++k) {
-                while (sg < s_hi && seg_off[sg + 1] <= i0 + k) ++sg;
+                while (k >= next) {
+                    ++sg;
+                    next = sg < (uint32_t)s_hi ? (int)(seg_off[sg + 1] - i0) : EPT;
+                }
                 seg_of[k] = sg;
             }
             for (int u = 0; u < U; ++u) {
+                const int32_t *anchor_u = anchor + (int64_t)u * nseg;
+                const float *scale_u = scale ? scale + (int64_t)u * nseg : nullptr;
                 uint4 v = *reinterpret_cast<const uint4 *>(src + (int64_t)u * ws_stride);
                 uint32_t w[4] = {v.x, v.y, v.z, v.w};
 #pragma unroll
-                for (int k = 0; k < EPT; ++k) acc[k] += value(symbol(w, k), u, seg_of[k]);
+                for (int k = 0; k < EPT; ++k) {
+                    asm volatile("" : "+v"(seg_of[k]));    // addresses made from it stay inside the loop (see above)
+                    const uint32_t s = symbol(w, k);
+                    float val = co3_code_value(s & cmask, anchor_u[seg_of[k]] - F + 1, M);
+                    val = __uint_as_float(__float_as_uint(val) | ((s >> EM) << 31));
+                    acc[k] += scale_u ? val / scale_u[seg_of[k]] : val;
+                }
             }
         }
 #pragma unroll
@@ -942,8 +959,9 @@ hipError_t co3_launch_ps_sum_tiled(const uint8_t *symt, int64_t n, int U, int64_
     unsigned blocks = (unsigned)(b < 16384 ? b : 16384);
     Co3LaunchTimer tm(CO3_K_PS_SUM, st);
     const size_t full_bytes = (size_t)U * (size_t)(1 << (1 + fmt.exp_bits + fmt.mant_bits)) * sizeof(float);
-    // Several tensors: the values in LDS pay from three users on (11.2 M elements in 62 tensors, E4M3, us with |
-    // without: one user 25.2 | 21.5, four 37.3 | 42.0, ten 68.7 | 90.3).
+    // Several tensors: the values in LDS pay from three users on (E4M3, us with | without: 11.2 M elements in 62 tensors,
+    // two users 24.1 | 24.5, three 27.9 | 30.6, sixteen 76 | 113; 11 M in 275 tensors, two 27.2 | 25.0, three 32.3 |
+    // 31.6, four 36.7 | 37.8, sixteen 95 | 113).
     const bool tables_pay = nseg > 1 && U >= 3;
 #define CO3_SUM_LAUNCH(T, P, BYTES)                                                                                \
     hipLaunchKernelGGL((k_ps_sum_tiled<T, P>), dim3(blocks), dim3(threads), BYTES, st, symt, n, U, ws_stride,     \

@@ -161,6 +161,34 @@ def test_average_of_several_tensors(co3, layout, E, M, U):
     assert np.array_equal(pipe.avg[:n].cpu().numpy().view(np.uint32), want.view(np.uint32))
 
 
+@pytest.mark.parametrize("scaled", [False, True])
+@pytest.mark.parametrize("E,M", [(3, 0), (4, 3)])
+@pytest.mark.parametrize("U", [1, 2, 4])
+def test_average_over_empty_and_single_element_tensors(co3, E, M, U, scaled):
+    """Runs that hold many tensors, several beginning at the same element, beside runs inside one."""
+    r = np.random.default_rng(U)
+    sizes = np.concatenate([r.choice([0, 0, 1, 2, 40], 2000), [0] * 300, [20_000, 0, 1, 0], r.choice([0, 1], 700)])
+    seg = inp.seg_offsets(sizes)
+    n, fmt, f = int(seg[-1]), co3.Fmt(E, M), oracle.Fmt(E, M)
+    pipe = co3.Co3Pipeline(U, n, fmt, seg_off=seg)
+    s = r.integers(0, fmt.K, (U, n)).astype(np.uint8)
+    pipe.sym[:, :n] = torch.from_numpy(s).cuda()
+    co3.binding.histogram(pipe.sym, n, fmt, pipe.counts)
+    pipe.build()
+    pipe.encode()
+    anchor = r.integers(-20, 20, (U, len(sizes))).astype(np.int32)
+    scale = r.uniform(0.5, 40.0, (U, len(sizes))).astype(np.float32) if scaled else None
+    pipe.anchor[:] = torch.from_numpy(anchor)
+    if scaled:
+        co3.binding.ps_aggregate_scaled(pipe.words, pipe.chunk_bitoff, pipe.chunk_syms, pipe.codes, fmt, n, U, pipe.anchor,
+                                        torch.from_numpy(scale).cuda(), pipe.avg, pipe.agg_ws, pipe.status, seg_off=pipe.seg_off)
+    else:
+        pipe.aggregate()
+    assert pipe.poll() == 0
+    want = oracle.aggregate(s, anchor, f, seg, scale)
+    assert np.array_equal(pipe.avg[:n].cpu().numpy().view(np.uint32), want.view(np.uint32))
+
+
 @pytest.mark.parametrize("E,M", [(3, 0), (4, 3)])
 @pytest.mark.parametrize("n", [1, 1024, 16_384, 16_385, 64 * 16_384 - 1, 64 * 16_384, 64 * 16_384 + 1])
 def test_group_offsets_in_the_packer(co3, n, E, M):
