@@ -1,17 +1,15 @@
-// Huffman code construction (Sec. III (ii)) by one workgroup of CO3_HB_BLOCK lanes: code lengths by the
+// Huffman code construction (Sec. III (ii)) by one workgroup of 1024 or 256 lanes: code lengths by the
 // two-queue merge, canonical codewords, and the decoder tables of the code blob, from K <= 256 integer weights.
 //
-// One code per workgroup and a chip that is otherwise idle: what counts is the length of the dependent chain.
-// The merge used to take one step per merged node in one lane (255 steps of about 250 cycles at K = 256); it
-// now takes one round per level of the tree (20 - 24 rounds of 650 - 1,250 cycles on the 8-bit formats, 9 at
-// K = 16), and the steps around it no longer hold loops over LDS entries one at a time.  Launch to end by
-// the library's timer, before | now: 11.2 M elements in E4M3 58 | 23 us (with the ragged end of the vector), ten
-// codes at K = 256 54 | 21 us, K = 32 18 | 13 us, K = 16 17 | 15 us.
+// A few codes on a chip that is otherwise idle: what counts is the length of the dependent chain.  With one merged
+// node a step in one lane, and loops over LDS entries one at a time around it, K = 256 took 255 steps of about 250
+// cycles; it now takes one round per level of the tree (20 - 24 rounds of 650 - 1,250 cycles on the 8-bit formats).
+// Launch to launch in a graph, before | now: K = 256 52 | 19 us, 64 22 | 16, 32 15.6 | 13.5, 16 11.6 | 10.9; with the
+// ragged end of 11.2 M elements in E4M3 58 | 23 us.
 #pragma once
 #include "co3_dev.h"
 
-#define CO3_HB_BLOCK 1024
-#define CO3_HB_WAVES (CO3_HB_BLOCK / CO3_WAVE)
+#define CO3_HB_BLOCK 1024       // lanes for a few codes; many take 256 (co3_launch_build_code)
 #define CO3_LEN_CAP 62          // lengths are clipped here; above CO3_MAX_CODE_LEN the status word says so
 
 template <int V> struct Co3Const { static constexpr int value = V; };
@@ -241,7 +239,9 @@ __device__ __forceinline__ void co3_leaf_depths(Co3BuildLds &L, const int lane, 
     if (lane == 0) L.maxlen = longest;
 }
 
-// weight: of symbol tid, for tid < 256 (0 from K on).  out: the user's code blob.  All lanes of the workgroup call it.
+// weight: of symbol tid, for tid < 256 (0 from K on).  out: the user's code blob.  All BLOCK lanes of the workgroup
+// call it.
+template <int BLOCK>
 __device__ __forceinline__ void co3_build_code_group(Co3BuildLds &L, const int tid, const uint32_t weight, const int K,
                                                      Co3Code *out, int32_t *status)
 {
@@ -258,11 +258,13 @@ __device__ __forceinline__ void co3_build_code_group(Co3BuildLds &L, const int t
     }
     __syncthreads();
 
-    // leaves in (weight, symbol) order: a symbol's place is the number of keys below its own; four lanes per
-    // symbol, each comparing with a quarter of the keys (all lanes of a wavefront read the same two entries at a
+    // leaves in (weight, symbol) order: a symbol's place is the number of keys below its own; PARTS lanes per
+    // symbol, each comparing with its share of the keys (all lanes of a wavefront read the same two entries at a
     // time, a broadcast)
+    constexpr int PARTS = BLOCK / 256;
+    static_assert(PARTS * 256 == BLOCK, "whole alphabets of lanes");
     if ((tid & 255) < (K + CO3_WAVE - 1) / CO3_WAVE * CO3_WAVE) {
-        const int sy = tid & 255, part = tid >> 8, per = (K + 7) / 8 * 2;      // keys per part, an even number
+        const int sy = tid & 255, part = tid >> 8, per = (K + 2 * PARTS - 1) / (2 * PARTS) * 2;      // keys per part, an even number
         const double mine = L.key[sy];
         const int k0 = part * per, k1 = k0 + per < 256 ? k0 + per : 256;
         uint32_t below = 0;
@@ -292,7 +294,7 @@ __device__ __forceinline__ void co3_build_code_group(Co3BuildLds &L, const int t
         else L.leaf_w[r] = (double)weight;
         L.leaf_sym[r] = (uint8_t)tid;
     }
-    for (int j = tid; j < 256 + CO3_WAVE; j += CO3_HB_BLOCK) {
+    for (int j = tid; j < 256 + CO3_WAVE; j += BLOCK) {
         if (small) {
             if (j >= nact) reinterpret_cast<uint32_t *>(L.leaf_w)[j] = Co3MergeU32::none();
             reinterpret_cast<uint32_t *>(L.node_w)[j] = Co3MergeU32::none();
@@ -362,7 +364,8 @@ __device__ __forceinline__ void co3_build_code_group(Co3BuildLds &L, const int t
         if (l) L.sorted[base_l + rank] = (uint8_t)tid;
         out->len[tid] = (uint8_t)l;
         out->enc[tid] = l ? ((first_l + rank) << 6) | (uint64_t)l : 0ull;
-    } else if (wave == 4) {
+    }
+    if (wave == BLOCK / CO3_WAVE - 1) {       // (with 1024 lanes one that has no symbols)
         out->first_code[lane] = first;
         out->count[lane] = (uint16_t)cnt;
         out->base[lane] = (uint16_t)base;
@@ -405,7 +408,7 @@ __device__ __forceinline__ void co3_build_code_group(Co3BuildLds &L, const int t
     auto entry = [&](uint32_t i, uint32_t k) -> uint32_t {
         return k > lut_bits ? 0u : (k << 8) | L.sorted[(uint32_t)((int)(i >> (lut_bits - k)) + L.at[k]) & 255u];
     };
-    for (uint32_t i = 4 * tid; i < (1u << lut_bits); i += 4 * CO3_HB_BLOCK) {
+    for (uint32_t i = 4 * tid; i < (1u << lut_bits); i += 4 * BLOCK) {
         const uint32_t ka = length_of(i), kd = length_of(i + 3);
         uint32_t kb = ka, kc = ka;
         if (ka != kd) {

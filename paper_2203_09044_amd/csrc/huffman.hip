@@ -5,14 +5,15 @@
 #include "kernels.h"
 
 // The weights of a user -> its code.
-__global__ __launch_bounds__(CO3_HB_BLOCK) void k_build_code(const uint32_t *__restrict__ weights, int K, char *codes,
+template <int BLOCK>
+__global__ __launch_bounds__(BLOCK) void k_build_code(const uint32_t *__restrict__ weights, int K, char *codes,
                                                               int32_t *status)
 {
     const int u = blockIdx.x;
     const int tid = threadIdx.x;
     __shared__ Co3BuildLds lds;
     const uint32_t wt = tid < K ? weights[(size_t)u * K + tid] : 0u;
-    co3_build_code_group(lds, tid, wt, K, reinterpret_cast<Co3Code *>(codes + (size_t)u * CO3_CODE_BYTES), status);
+    co3_build_code_group<BLOCK>(lds, tid, wt, K, reinterpret_cast<Co3Code *>(codes + (size_t)u * CO3_CODE_BYTES), status);
 }
 
 // What is left of a user's steps before compression when a resident grid has converted everything but the
@@ -98,7 +99,7 @@ __global__ __launch_bounds__(CO3_HB_BLOCK) void k_user_finish(const float *__res
         wt = hist[tid];
         counts[(size_t)u * K + tid] = wt;
     }
-    co3_build_code_group(lds, tid, wt, K, reinterpret_cast<Co3Code *>(codes + (size_t)u * CO3_CODE_BYTES), status);
+    co3_build_code_group<CO3_HB_BLOCK>(lds, tid, wt, K, reinterpret_cast<Co3Code *>(codes + (size_t)u * CO3_CODE_BYTES), status);
 }
 
 hipError_t co3_launch_user_finish(const float *g, float *err, uint8_t *sym, int64_t n, int64_t n_full, int64_t stride, int U,
@@ -117,7 +118,14 @@ hipError_t co3_launch_build_code(const uint32_t *weights, int U, int K, void *co
 {
     if (U <= 0) return hipSuccess;
     Co3LaunchTimer tm(CO3_K_BUILD, st);
-    hipLaunchKernelGGL(k_build_code, dim3(U), dim3(CO3_HB_BLOCK), 0, st, weights, K, reinterpret_cast<char *>(codes),
-                       status);
+    // More codes than two large workgroups per compute unit hold at a time: what counts is how many are under way, and
+    // one wavefront does the merge (256 | 1024 lanes, 400, 700 and 4,000 codes: K = 256 25 | 23 us, 27 | 40, 70 | 164;
+    // K = 32 17.8 | 17.5, 19 | 30, 46 | 120).
+    const int known = co3_device_cus(), cus = known > 0 ? known : 256;
+    if (U > 2 * cus)
+        hipLaunchKernelGGL(k_build_code<256>, dim3(U), dim3(256), 0, st, weights, K, reinterpret_cast<char *>(codes), status);
+    else
+        hipLaunchKernelGGL(k_build_code<CO3_HB_BLOCK>, dim3(U), dim3(CO3_HB_BLOCK), 0, st, weights, K,
+                           reinterpret_cast<char *>(codes), status);
     return hipGetLastError();
 }

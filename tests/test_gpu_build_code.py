@@ -73,3 +73,27 @@ def test_code_of_edge_weights(co3, name, weights):
     nw = (total + 63) // 64
     assert np.array_equal(d_words.cpu().numpy().view(np.uint64)[:nw], words[:nw])
     assert np.array_equal(back[:n].cpu().numpy(), sym)
+
+
+@pytest.mark.parametrize("E,M", [(1, 0), (2, 0), (3, 0), (3, 1), (4, 3)])
+def test_many_codes_in_one_call(co3, E, M):
+    """More codes than two large workgroups per compute unit take smaller ones: the same blobs byte for byte as in
+    calls of a few codes, and the oracle's lengths.  Up to 16 leaves and more, weights below and above 2^30 in all."""
+    B = co3.binding
+    fmt, r = co3.Fmt(E, M), np.random.default_rng(E * 8 + M)
+    U = 2 * torch.cuda.get_device_properties(0).multi_processor_count + 1
+    w = (r.random((U, fmt.K)) ** r.integers(1, 12, (U, 1)) * 10.0 ** r.integers(1, 10, (U, 1))).astype(np.int64)
+    w = np.where(r.random((U, fmt.K)) < r.random((U, 1)), np.minimum(w, 2**32 - 1), r.integers(0, 3, (U, fmt.K)))
+    w[:20] *= np.arange(fmt.K) < np.arange(20)[:, None]                   # 0 to 19 leaves
+    w = w.astype(np.uint32)
+    d = torch.from_numpy(w.view(np.int32)).cuda()
+    status = torch.zeros(1, dtype=torch.int32, device="cuda")
+    many, few = (torch.zeros((U, B.CODE_BYTES), dtype=torch.uint8, device="cuda") for _ in range(2))
+    B.build_code(d, U, fmt, many, status)
+    for u in range(0, U, 100):
+        B.build_code(d[u:u + 100], min(100, U - u), fmt, few[u:u + 100], status)
+    assert B.poll_status(status) == 0
+    assert torch.equal(many, few)
+    got = many[:, :256].cpu().numpy()
+    for u in range(U):
+        assert np.array_equal(got[u, :fmt.K], np.asarray(oracle.huffman_lengths(w[u]), dtype=np.uint8)), u
