@@ -4,12 +4,13 @@
 // A few codes on a chip that is otherwise idle: what counts is the length of the dependent chain.  With one merged
 // node a step in one lane, and loops over LDS entries one at a time around it, K = 256 took 255 steps of about 250
 // cycles; it now takes one round per level of the tree (20 - 24 rounds of 650 - 1,250 cycles on the 8-bit formats).
-// Launch to launch in a graph, before | now: K = 256 52 | 19 us, 64 22 | 16, 32 15.6 | 13.5, 16 11.6 | 10.9; with the
-// ragged end of 11.2 M elements in E4M3 58 | 23 us.
+// At most 16 leaves still take a step per node.  Launch to launch in a graph, before | now: K = 256 52 | 19 us, 64
+// 22 | 16, 32 15.6 | 13.5, 16 11.6 | 8.8, 8 6.3 | 6.4; with the ragged end of 11.2 M elements in E4M3 58 | 23 us.
 #pragma once
 #include "co3_dev.h"
 
 #define CO3_HB_BLOCK 1024       // lanes for a few codes; many take 256 (co3_launch_build_code)
+#define CO3_HB_STEPS 16         // most leaves that are merged a node a step
 #define CO3_LEN_CAP 62          // lengths are clipped here; above CO3_MAX_CODE_LEN the status word says so
 
 template <int V> struct Co3Const { static constexpr int value = V; };
@@ -198,6 +199,31 @@ __device__ __forceinline__ void co3_merge_rounds(Co3BuildLds &L, const int lane,
     }
 }
 
+// The two-queue merge of few leaves, one node a step in one lane.  A step reads the two fronts of each queue and
+// takes one of three outcomes: two leaves, two nodes, or the first leaf with the first node.  A skewed code of few
+// symbols has nearly as many levels as nodes, and a round costs three steps or more: steps | rounds, skewed weights,
+// K = 8 6.4 | 7.9 us, 16 8.8 | 10.9, 32 12.1 | 13.5; but the model's law at K = 32 10.3 | 8.6, K = 64 16.4 | 12.3.
+template <class T>
+__device__ __forceinline__ void co3_merge_steps(Co3BuildLds &L, const int lane, const int nact)
+{
+    typedef typename T::W W;
+    const W *leaf_w = reinterpret_cast<const W *>(L.leaf_w);
+    W *node_w = reinterpret_cast<W *>(L.node_w);
+    if (lane == 0) {
+        int q1 = 0, q2 = 0;
+        for (int ne = 0; ne < nact - 1; ++ne) {
+            const W l0 = leaf_w[q1], l1 = leaf_w[q1 + 1], n0 = node_w[q2], n1 = node_w[q2 + 1];
+            const bool leaves = l1 <= n0, nodes = !leaves && n1 < l0;
+            L.parent[nodes ? 256 + q2 + 1 : q1] = (uint16_t)ne;
+            L.parent[leaves ? q1 + 1 : 256 + q2] = (uint16_t)ne;
+            node_w[ne] = leaves ? l0 + l1 : nodes ? n0 + n1 : l0 + n0;
+            q1 += leaves ? 2 : nodes ? 0 : 1;
+            q2 += leaves ? 0 : nodes ? 2 : 1;
+        }
+    }
+    co3_lds_order();
+}
+
 // Code lengths = depths of the leaves, by the same wavefront: every node's way up is doubled until it ends at the
 // root (log2 of the depth steps instead of one step per level).
 __device__ __forceinline__ void co3_leaf_depths(Co3BuildLds &L, const int lane, const int nact)
@@ -305,7 +331,9 @@ __device__ __forceinline__ void co3_build_code_group(Co3BuildLds &L, const int t
     }
     __syncthreads();
     if (wave == 0) {
-        if (small) co3_merge_rounds<Co3MergeU32>(L, lane, nact);
+        if (nact <= CO3_HB_STEPS && small) co3_merge_steps<Co3MergeU32>(L, lane, nact);
+        else if (nact <= CO3_HB_STEPS) co3_merge_steps<Co3MergeF64>(L, lane, nact);
+        else if (small) co3_merge_rounds<Co3MergeU32>(L, lane, nact);
         else co3_merge_rounds<Co3MergeF64>(L, lane, nact);
         co3_leaf_depths(L, lane, nact);
     }
