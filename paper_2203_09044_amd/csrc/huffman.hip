@@ -120,9 +120,10 @@ hipError_t co3_launch_build_code(const uint32_t *weights, int U, int K, void *co
     Co3LaunchTimer tm(CO3_K_BUILD, st);
     // More codes than two large workgroups per compute unit hold at a time: what counts is how many are under way, and
     // one wavefront does the merge (256 | 1024 lanes, 400, 700 and 4,000 codes: K = 256 25 | 23 us, 27 | 40, 70 | 164;
-    // K = 32 17.8 | 17.5, 19 | 30, 46 | 120).
+    // K = 32 17.8 | 17.5, 19 | 30, 46 | 120).  The tables of up to 8 symbols gain nothing from more lanes (300 codes of
+    // K = 8 7.2 | 7.9).
     const int known = co3_device_cus(), cus = known > 0 ? known : 256;
-    if (U > 2 * cus)
+    if (U > 2 * cus || K <= 8)
         hipLaunchKernelGGL(k_build_code<256>, dim3(U), dim3(256), 0, st, weights, K, reinterpret_cast<char *>(codes), status);
     else
         hipLaunchKernelGGL(k_build_code<CO3_HB_BLOCK>, dim3(U), dim3(CO3_HB_BLOCK), 0, st, weights, K,
