@@ -1,6 +1,8 @@
-"""The code build merges in rounds: the sizes at which a round changes its form (more than 63 leaves or nodes),
-the weights at which its arithmetic does (2^30 in all), ties, and very deep and very flat trees, each against the
-oracle; the code is then used to encode and decode, so that codewords and decoder tables are the canonical ones."""
+"""The code build merges a node a step (up to 16 leaves) or in rounds: the sizes at which one follows the other and
+at which a round changes its form (more than 63 leaves or nodes), the weights at which the arithmetic does (2^30 in
+all), ties, and very deep and very flat trees, each against the oracle; the code is then used to encode and decode, so
+that codewords and decoder tables are the canonical ones.  (Symbols are drawn uniformly there; codewords beyond the
+decoder's table in every order are the decoder's own test.)"""
 import numpy as np
 import pytest
 

@@ -1,6 +1,7 @@
-"""The decoder's registers-held window and its workgroup sizes: stretches of codewords beyond the table in runs
-that otherwise hit it, at one to eight wavefronts a workgroup, and the average with the values of a tensor in LDS
-against an anchor per run or element.  Everything is defined bit for bit."""
+"""The decoder's registers-held window and its workgroup sizes: stretches of codewords beyond the table (of up to 38
+bits, drawn at random) in runs that otherwise hit it, at one to eight wavefronts a workgroup; codewords of up to 52
+bits in every order around hits; stored tables of a shorter prefix; and the average with the values of a tensor in
+LDS against an anchor per run or element.  Everything is defined bit for bit."""
 import numpy as np
 import pytest
 
