@@ -12,7 +12,8 @@
  *   - every pointer is a DEVICE pointer owned by the caller; the library never
  *     allocates or frees device memory and keeps no state between calls.  The
  *     exceptions, all process-wide: the fixed workspace of co3_encode_static, the
- *     poll limit set by co3_set_exchange_spin_limit (an atomic word), and, only
+ *     poll limit set by co3_set_exchange_spin_limit (an atomic word), what has been
+ *     looked up once per device (compute units, LDS granted; atomic words), and, only
  *     while co3_timing_enable has switched it on, a pool of events for the
  *     per-kernel timer (not thread-safe: a diagnostic for single-threaded use);
  *   - `stream` is a hipStream_t passed as void* (NULL = the default stream); the
