@@ -730,10 +730,9 @@ __global__ __launch_bounds__(DL_BLOCK) void k_decode_layers(const uint64_t *__re
 //
 // Bound by latency and, with many users, by issue: how many wavefronts a SIMD holds counts.  They are set by the
 // runs that straddle tensors, though few do: with an address per element kept from user to user, and the 64-bit
-// comparisons that found its tensor, the kernel took 227 to 230 registers (NIB) and 132 to 135; now 128 to 132
-// and 82 to 86.  Average of
-// 11.2 M elements in 62 tensors, before | now: E3M0 two users 32 | 29 us, ten 70 | 55; E4M3 two 27 | 24, three
-// 36 | 28, ten 69 | 54.  In 33,333 tensors of three: E3M0 ten users 51 | 50.
+// comparisons that found its tensor, the kernel took 227 to 230 registers (NIB) and 132 to 135; now 128 to 132 and
+// 82 to 86.  Average of 11.2 M elements in 62 tensors, before | now: E3M0 two users 32 | 29 us, ten 70 | 55; E4M3
+// two 27 | 24, three 36 | 28, ten 69 | 54.  In 33,333 tensors of three: E3M0 ten users 51 | 50.
 template <int TABLE, bool NIB>
 __global__ __launch_bounds__(PT_WAVES(NIB) * CO3_WAVE) __attribute__((amdgpu_waves_per_eu(NIB ? 3 : 4)))
 void k_ps_sum_tiled(const uint8_t *__restrict__ symt, int64_t n, int U, int64_t ws_stride, int chunk_syms, int64_t nruns,
