@@ -1,9 +1,9 @@
 // Compression h_Hf (Algorithm 1, user side): coded size of every tile of 1024 symbols, exclusive scan
-// of the tile sizes per user, then bit packing.  In the packing pass one wavefront owns one tile (16
-// symbols per lane): it looks the codewords up, scans the lengths, packs its bits in an LDS staging
-// window and writes every 64-bit word whose first bit lies inside the tile -- completing the last
-// such word with the leading codewords of the following symbols, so that each word of the stream is
-// written exactly once, by one wavefront, with plain coalesced stores.
+// of the tile sizes per user, then bit packing.  In the packing pass one wavefront takes one tile (16
+// symbols per lane): it looks the codewords up, scans the lengths and packs its bits in an LDS staging
+// window -- its own, or one of four consecutive tiles -- from which every 64-bit word whose first bit
+// lies in the window's tiles leaves, the last one completed with the leading codewords of the following
+// symbols, so that each word of the stream is written exactly once, with plain coalesced stores.
 #include "co3_dev.h"
 #include "kernels.h"
 
@@ -14,6 +14,8 @@
 #define EN_LSYM 16                             // symbols per lane
 #define EN_STAGE_WORDS 128                     // staging window: 8192 bits = 8 bits/symbol on average
 static_assert(CO3_WAVE * EN_LSYM == CO3_PACK_SYMS, "tile geometry");
+#define EN_WG_SYMS (EN_WAVES * CO3_PACK_SYMS)  // symbols of a workgroup's tiles
+#define EN_WG_WORDS 640                        // staging window of a workgroup: 10 bits/symbol on average
 
 __device__ __forceinline__ const Co3Code *code_of(const void *codes, int u)
 {
@@ -405,113 +407,253 @@ __device__ __forceinline__ void stage_bits(unsigned long long *stage, int64_t wi
     if (o + nb > 64 && w + 1 >= 0 && w + 1 < EN_STAGE_WORDS) atomicOr(&stage[w + 1], (unsigned long long)(v << (64 - o)));
 }
 
-// LAYERS = false: one code per user (codes[u]), its table shared by the workgroup.  LAYERS = true: one
-// code per tensor shared by all users (codes[tensor]); each wavefront keeps the table of its tile's
-// tensor, and a tile that straddles tensors (look-ahead included) reads its entries from the code
-// blobs, tensor by element.
-// The per-user form is compiled for eight wavefronts per SIMD (64 registers; a few spills on the rarely taken
-// paths): the kernel is bound by the latency of its per-tile chain, and residency is what hides it (C3:
-// 61 -> 55 us against six wavefronts per SIMD).
+// ---- whole blocks of four tiles packed by a workgroup together ---------------------------------
+// A window per wavefront made the packer short-lived wavefronts of 7,500 cycles, half of them spent before the first
+// codeword: a workgroup takes up to four blocks in a row, its tables built once, the next block's symbols requested
+// while one is packed, one barrier a block, and only the last block looks ahead: the unfinished last word of a block
+// is handed to the window of the next.  What is the same for a wavefront is kept in scalar registers, and codewords are
+// joined in table entries of 32 bits (16 symbols of a lane: 267 -> 175 vector instructions in an 8-bit format, 237 -> 117
+// with two symbols per byte).  Fewer instructions alone gave nothing: a workgroup per block with the same packing took
+// 198 and 49 us below.  10 x 11.2 M E3M0 52 -> 37 us, E4M3 57 -> 45; 16 x 25 M E4M3 199 -> 158 (737 MB at 4.7 TB/s, the
+// rate of a copy); 4 x 11.2 M E4M3 under shared codes 50 -> 35.
 //
-// SCAN: groupoff holds the sizes of at most 64 groups as the sizes pass left them.  Every wavefront takes them with
-// one load, beside those it makes anyway, and scans them in registers; the first one of a user writes what the
-// scan kernel would.  That saves the kernel (3.3 us and its place in a chain of small ones: one user of 65,536
-// elements 53.9 -> 50.0 us a pass).  With up to 682 groups a form of this took 59 us against 51 and the kernel's 5.
-template <bool LAYERS, bool SCAN>
-__global__ __launch_bounds__(EN_BLOCK) __attribute__((amdgpu_waves_per_eu(LAYERS ? 5 : 8, LAYERS ? 5 : 8)))
-void k_enc_pack(const uint8_t *__restrict__ sym, int64_t n, int64_t stride, const void *__restrict__ codes, int K,
-                const int64_t *__restrict__ seg_off_g, int nseg, const uint64_t *__restrict__ tileoff, int64_t nblk,
-                const uint64_t *__restrict__ groupoff, int64_t ngrp, uint64_t *__restrict__ words, int64_t cap_words,
-                int chunk_syms, uint64_t *__restrict__ chunk_bitoff, int64_t nchunks, int sym_nib,
-                uint64_t *__restrict__ total_bits, int32_t *status)
+// An entry is codeword << 8 | length; a codeword of 24 bits or more has only its length there and the top bit set.  A
+// lane with such a codeword, or with two neighbours of 32 bits together, packs its symbols one by one.
+#define EN_FAR_PAIR 0x60u                      // bits of the sum of two lengths
+#define EN_FAR_ENTRY 0x80000000u
+struct PackLds {
+    uint64_t enc[256];                         // as in the code
+    uint32_t tab[256];                         // per symbol; symbols two per byte: per pair of symbols
+    unsigned long long win[2][EN_WG_WORDS + 2]; // word r of a block's window at EN_WG_WORDS - 1 - r
+};
+
+__device__ __forceinline__ uint32_t pack_entry(uint64_t code, uint32_t l)
 {
-    const int u = blockIdx.y;
-    const bool nib = !LAYERS && sym_nib != 0;
-    __shared__ uint64_t enc_all[LAYERS ? EN_WAVES * 256 : 256];
-    __shared__ uint64_t penc_s[LAYERS ? 1 : 256];        // codeword pairs, symbols two per byte
-    __shared__ unsigned long long stage_all[EN_WAVES][EN_STAGE_WORDS];
-    __shared__ int64_t seg_cache[LAYERS ? CO3_SEG_CACHE : 1];
-    const int lane = threadIdx.x & (CO3_WAVE - 1);
-    const int wave = threadIdx.x / CO3_WAVE;
-    const int64_t tb = (int64_t)blockIdx.x * EN_WAVES + wave;      // the wavefront's tile: elements [t0, t1)
+    return l >= 24u ? EN_FAR_ENTRY | l : ((uint32_t)code << 8) | l;
+}
+
+#define EN_WIN_BITS ((EN_WG_WORDS + 2) * 64u)   // distance of the two windows
+
+// ORs the `nb` <= 64 bits of v (right-aligned) into the windows.  d: distance of their start from the end of the first
+// window (for the second one EN_WIN_BITS more), on return that of their end; what of v lies before the word that holds
+// their end goes to the word before, which is the next one in the array.
+__device__ __forceinline__ void pack_put(PackLds &L, uint64_t v, uint32_t nb, uint32_t &d)
+{
+    d -= nb;
+    unsigned long long *w = L.win[0] + (d >> 6);
+    atomicOr(w, (unsigned long long)(v << (d & 63u)));
+    if ((d & 63u) + nb > 64u) atomicOr(w + 1, (unsigned long long)(v >> ((0u - d) & 63u)));
+}
+
+// `blocks` blocks from element i0 on, all of one code.  where(group_base, end_bit): stream positions of their group of
+// tiles and of their end (called behind the first barrier, when what it is made from has arrived with the symbols and
+// the table); toff: positions of their tiles in the group.  Returns false (to all threads) where a block does not fit
+// its window or the stream its capacity; nothing has been written then.
+template <bool NIB, class Where>
+__device__ __forceinline__ bool pack_blocks(PackLds &L, const uint8_t *su, const Co3Code *cd, int K, int64_t n, int64_t i0,
+                                            int blocks, int wave, int lane, Where where, const uint64_t *__restrict__ toff,
+                                            uint64_t *__restrict__ wu, int64_t cap_words, int chunk_syms,
+                                            uint64_t *__restrict__ chunk_off)
+{
+    constexpr int G = EN_LSYM / 4;
+    const int64_t iw = i0 + (int64_t)wave * CO3_PACK_SYMS;
+    const uint8_t *src = su + (NIB ? iw >> 1 : iw);                      // uniform
+    const uint32_t lane_at = (uint32_t)lane * (NIB ? EN_LSYM / 2 : EN_LSYM);
+    auto load = [&]() -> uint4 {
+        if (NIB) {
+            const uint2 a = *reinterpret_cast<const uint2 *>(src + lane_at);
+            return make_uint4(a.x, a.y, 0u, 0u);
+        }
+        return *reinterpret_cast<const uint4 *>(src + lane_at);
+    };
+    uint4 nxt = load();
+    // the symbols that follow the last block: their codewords complete its last word
+    const int64_t i_end = i0 + (int64_t)blocks * EN_WG_SYMS;
+    const bool ahead = wave == EN_WAVES - 1 && lane < CO3_WAVE - 1 && i_end + lane < n;
+    const uint32_t next_sym = ahead ? load_sym1(su, i_end + lane, NIB) : 0u;
+    {
+        const int j = threadIdx.x;
+        static_assert(EN_BLOCK == 256, "a table entry per thread");
+        const uint64_t e = j < K ? cd->enc[j] : 0ull;
+        L.enc[j] = e;
+        if (NIB) {
+            const int lo = j & 15, hi = j >> 4;
+            const uint64_t e0 = lo < K ? cd->enc[lo] : 0ull, e1 = hi < K ? cd->enc[hi] : 0ull;
+            const uint32_t l1 = (uint32_t)(e1 & 63u);
+            L.tab[j] = pack_entry(((e0 >> 6) << l1) | (e1 >> 6), (uint32_t)(e0 & 63u) + l1);
+        } else {
+            L.tab[j] = pack_entry(e >> 6, (uint32_t)(e & 63u));
+        }
+        for (int q = j; q < EN_WG_WORDS + 2; q += EN_BLOCK) reinterpret_cast<ulonglong2 *>(L.win)[q] = make_ulonglong2(0ull, 0ull);
+    }
+    const uint64_t off0 = toff[0];
+    __syncthreads();
+    uint64_t group_base, end_bit;
+    where(group_base, end_bit);
+    {
+        bool fits = (int64_t)((end_bit + 63) >> 6) <= cap_words;
+        uint64_t from = off0;
+        for (int k = 1; k <= blocks; ++k) {
+            const uint64_t to = k < blocks ? toff[k * EN_WAVES] : end_bit - group_base;
+            fits = fits && to - from <= EN_WG_WORDS * 64u - 63u;
+            from = to;
+        }
+        if (!fits) {
+            __syncthreads();                   // the general path uses the same LDS
+            return false;
+        }
+    }
+
+    uint64_t base = group_base + off0;
+    bool foreign = (base & 63u) != 0u;         // the window's first word begins before element i0
+    const bool chunk_lane = ((lane * EN_LSYM) & (chunk_syms - 1)) == 0;  // (chunk sizes are powers of two)
+    const uint32_t chunk_sh = (uint32_t)__builtin_ctz((unsigned)chunk_syms);
+    const uint32_t chunk_at = (uint32_t)(lane * EN_LSYM) >> chunk_sh;
+    int64_t tile_i = iw;
+    const uint64_t *tp = toff;
+#pragma unroll 1
+    for (int k = 0; k < blocks; ++k) {
+        const bool last = k + 1 == blocks;
+        const uint32_t s[4] = {nxt.x, nxt.y, nxt.z, nxt.w};
+        src += NIB ? EN_WG_SYMS / 2 : EN_WG_SYMS;
+        if (!last) nxt = load();
+        const uint32_t tile_rel = (uint32_t)tp[wave] - (uint32_t)tp[0];
+        const uint64_t base_next = last ? end_bit : group_base + tp[EN_WAVES];
+        tp += EN_WAVES;
+        const uint32_t base_bit = (uint32_t)base & 63u;
+        const uint32_t win = k & 1 ? EN_WIN_BITS : 0u;
+
+        // codewords of four symbols joined, right-aligned
+        uint64_t run[G];
+        uint32_t nb[G], far_pair = 0u, far_entry = 0u;
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+            if (NIB) {                         // two pairs of codewords from the table
+                const uint32_t w = s[g >> 1] >> (16 * (g & 1));
+                const uint32_t e0 = L.tab[w & 0xffu], e1 = L.tab[(w >> 8) & 0xffu];
+                run[g] = ((uint64_t)(e0 >> 8) << (e1 & 63u)) | (e1 >> 8);
+                nb[g] = (e0 + e1) & 0xffu;
+                far_entry |= e0 | e1;
+            } else {                           // two pairs of codewords
+                const uint32_t e0 = L.tab[s[g] & 0xffu], e1 = L.tab[(s[g] >> 8) & 0xffu];
+                const uint32_t e2 = L.tab[(s[g] >> 16) & 0xffu], e3 = L.tab[s[g] >> 24];
+                const uint32_t t01 = e0 + e1, t23 = e2 + e3;
+                const uint32_t p01 = ((e0 >> 8) << (e1 & 31u)) | (e1 >> 8), p23 = ((e2 >> 8) << (e3 & 31u)) | (e3 >> 8);
+                run[g] = ((uint64_t)p01 << (t23 & 63u)) | p23;
+                nb[g] = (t01 + t23) & 0xffu;
+                far_pair |= t01 | t23;
+                far_entry |= e0 | e1 | e2 | e3;
+            }
+        }
+        const uint32_t n01 = nb[0] + nb[1], n23 = nb[2] + nb[3];
+        const uint32_t mybits = n01 + n23;
+        const uint32_t pos = base_bit + tile_rel + wave_scan_incl_u32(mybits, lane) - mybits;
+        if ((tile_i & (int64_t)(chunk_syms - 1) & ~(int64_t)(CO3_PACK_SYMS - 1)) == 0) {       // uniform
+            // chunk index: stream position of every chunk that starts at this lane's first symbol
+            if (chunk_lane) (chunk_off + (tile_i >> chunk_sh))[chunk_at] = (base - base_bit) + pos;
+        }
+        tile_i += EN_WG_SYMS;
+        uint32_t d = win + EN_WG_WORDS * 64u - pos;
+        const uint32_t far = NIB ? ((n01 | n23) & 0x40u) | (far_entry & EN_FAR_ENTRY)
+                                 : (far_pair & EN_FAR_PAIR) | (far_entry & EN_FAR_ENTRY);
+        if (far == 0u) {
+            if (NIB) {
+                pack_put(L, (run[0] << (nb[1] & 63u)) | run[1], n01, d);
+                pack_put(L, (run[2] << (nb[3] & 63u)) | run[3], n23, d);
+            } else {
+#pragma unroll
+                for (int g = 0; g < G; ++g) pack_put(L, run[g], nb[g], d);
+            }
+        } else {
+#pragma unroll 1
+            for (int c = 0; c < EN_LSYM; ++c) {
+                const int per = NIB ? 8 : 4, q = c / per;
+                const uint32_t w = q == 0 ? s[0] : q == 1 ? s[1] : q == 2 ? s[2] : s[3];
+                const uint64_t e = L.enc[(w >> (c % per * (32 / per))) & (NIB ? 0xfu : 0xffu)];
+                pack_put(L, e >> 6, (uint32_t)(e & 63u), d);
+            }
+        }
+        const uint32_t end = base_bit + (uint32_t)(base_next - base);    // of the block in the window
+        if (last && wave == EN_WAVES - 1 && (end & 63u)) {               // complete the last word
+            const uint64_t e = ahead ? L.enc[next_sym] : 0ull;
+            const uint32_t l = (uint32_t)(e & 63u);
+            const uint32_t o = wave_scan_incl_u32(l, lane) - l + (end & 63u);
+            uint32_t at = (win >> 6) + EN_WG_WORDS - 1 - (end >> 6);
+            asm volatile("" : "+v"(at));       // one word for all lanes: the compiler would gather them one by one
+            if (l && o < 64u) atomicOr(L.win[0] + at, (unsigned long long)(((e >> 6) << (64u - l)) >> o));
+        }
+        __syncthreads();
+        // Words leave in order; what has been read is cleared for the block after the next.
+        const uint32_t whole = end >> 6, nw = (end + 63u) >> 6;
+        uint64_t *dst = wu + (base >> 6);
+        for (uint32_t r = threadIdx.x; r < nw; r += EN_BLOCK) {
+            unsigned long long *w = L.win[0] + ((win >> 6) + EN_WG_WORDS - 1 - r);
+            const unsigned long long v = *w;
+            *w = 0ull;
+            if (r >= whole && !last) {         // (one thread) the unfinished word: the next window's first
+                uint32_t at = ((EN_WIN_BITS - win) >> 6) + EN_WG_WORDS - 1;
+                asm volatile("" : "+v"(at));
+                atomicOr(L.win[0] + at, v);
+            } else if (r != 0u || !foreign) dst[r] = v;
+        }
+        foreign = foreign && whole == 0u;
+        base = base_next;
+    }
+    return true;
+}
+
+// The general path: a wavefront packs its own tile tb, of any size and with any codes, through a window of its own.
+// s: the lane's 16 symbols, four a word; raw: a complete tile of symbols stored two per byte stays in that form, one
+// lookup per byte; next_sym: the symbols that follow the tile (their codewords complete its last word).
+__device__ __forceinline__ void load_tile(const uint8_t *su, bool nib, int64_t n, int64_t tb, int lane, uint32_t (&s)[4], uint2 &raw,
+                                          int &nvalid, uint32_t &next_sym, bool &has_next)
+{
+    const int64_t t0 = tb * CO3_PACK_SYMS;               // the wavefront's tile: elements [t0, t1)
+    const int64_t t1 = t0 + CO3_PACK_SYMS < n ? t0 + CO3_PACK_SYMS : n;
+    const int64_t i = t0 + (int64_t)lane * EN_LSYM;
+    s[0] = s[1] = s[2] = s[3] = 0u;
+    raw = make_uint2(0u, 0u);
+    nvalid = EN_LSYM;
+    if (t1 - t0 != CO3_PACK_SYMS) nvalid = i < t1 ? load_syms16(su, i, t1, s, nib) : 0;
+    else if (nib) raw = *reinterpret_cast<const uint2 *>(su + (i >> 1));
+    else load_syms16_full(su, i, nib, s);
+    has_next = t1 > t0 && lane < CO3_WAVE - 1 && t1 + lane < n;
+    next_sym = has_next ? load_sym1(su, t1 + lane, nib) : 0u;
+}
+
+// LAYERS: a tile that straddles tensors (look-ahead included) reads its entries from the code blobs, tensor by element.
+template <bool LAYERS>
+__device__ __forceinline__ void pack_tile(const uint32_t (&s)[4], uint2 raw, int nvalid, uint32_t next_sym, bool has_next, bool nib, int64_t n, const void *codes, int K, const int64_t *seg_off,
+                                          int nseg, int64_t tb, int lane, uint64_t *enc_s, const uint64_t *penc_s,
+                                          unsigned long long *stage, uint32_t maxlen, uint64_t B0, uint64_t *wu, int64_t cap_words,
+                                          int chunk_syms, uint64_t *chunk_off)
+{
     const int64_t t0 = tb * CO3_PACK_SYMS;
     const int64_t t1 = t0 + CO3_PACK_SYMS < n ? t0 + CO3_PACK_SYMS : n;
     const bool whole_tile = t1 - t0 == CO3_PACK_SYMS;
-    // Everything the wavefront reads from memory apart from the tables is requested first, so that its latency
-    // and that of the table load below (with its barrier) overlap.
-    const uint8_t *su = sym + (int64_t)u * (nib ? stride / 2 : stride);
-    uint64_t *wu = words + (int64_t)u * cap_words;
-    const int64_t i = t0 + (int64_t)lane * EN_LSYM;
-    const bool live = tb < nblk;                     // uniform: the wavefront has a tile
-    // a complete tile of symbols stored two per byte stays in that form: one lookup per byte below
+    const int64_t i = t0 + (int64_t)lane * EN_LSYM, i2 = t1 + lane;
     const bool raw_tile = nib && whole_tile;
-    uint32_t s[4] = {0u, 0u, 0u, 0u};
-    uint2 raw = make_uint2(0u, 0u);
-    int nvalid = EN_LSYM;
-    if (raw_tile) raw = *reinterpret_cast<const uint2 *>(su + (i >> 1));
-    else if (whole_tile) load_syms16_full(su, i, nib, s);
-    else nvalid = live && i < t1 ? load_syms16(su, i, t1, s, nib) : 0;
-    // the symbols that follow the tile (their codewords complete its last word): used at the end
-    const int64_t i2 = t1 + lane;
-    const bool has_next = live && t1 > t0 && lane < CO3_WAVE - 1 && i2 < n;
-    const uint32_t next_sym = has_next ? load_sym1(su, i2, nib) : 0u;
-    uint64_t group_base = 0;
-    uint32_t group_bits = 0;                         // SCAN: of group `lane`; 64 groups of codewords fit 32 bits
-    if (SCAN) group_bits = lane < (int)ngrp ? (uint32_t)groupoff[(int64_t)u * ngrp + lane] : 0u;
-    else if (live) group_base = groupoff[(int64_t)u * ngrp + tb / CO3_PACK_GROUP];
-    const uint64_t tile_base = live ? tileoff[(int64_t)u * nblk + tb] : 0ull;
 
-    const uint64_t *enc_s = LAYERS ? enc_all + wave * 256 : enc_all;
-    const int64_t *seg_off = seg_off_g;
-    uint32_t maxlen;
     bool one_tensor = true;
-    if (!LAYERS) {
-        const Co3Code *cd = code_of(codes, u);
-        for (int j = threadIdx.x; j < 256; j += blockDim.x) {
-            enc_all[j] = j < K ? cd->enc[j] : 0ull;
-            if (nib) {
-                const int lo = j & 15, hi = j >> 4;
-                const uint64_t e0 = lo < K ? cd->enc[lo] : 0ull, e1 = hi < K ? cd->enc[hi] : 0ull;
-                const uint32_t l1 = (uint32_t)(e1 & 63u);
-                penc_s[j] = ((((e0 >> 6) << l1) | (e1 >> 6)) << 6) | (uint64_t)((uint32_t)(e0 & 63u) + l1);
-            }
-        }
-        maxlen = cd->maxlen;
-        __syncthreads();
-        if (tb >= nblk) return;
-        if (SCAN) {
-            const uint32_t upto = wave_scan_incl_u32(group_bits, lane);
-            const int grp = __builtin_amdgcn_readfirstlane((int)(tb / CO3_PACK_GROUP));
-            group_base = grp ? (uint32_t)__builtin_amdgcn_readlane((int)upto, grp - 1) : 0u;
-            if (tb == 0 && lane == CO3_WAVE - 1) {   // the last lane holds the stream's length
-                total_bits[u] = upto;
-                chunk_bitoff[(int64_t)u * (nchunks + 1) + nchunks] = upto;
-                if (((uint64_t)upto + 63) / 64 > (uint64_t)cap_words) co3_raise(status, CO3_ECAP);
-            }
-        }
-    } else {
-        seg_off = co3_cache_segs(seg_off_g, nseg, seg_cache);
-        __syncthreads();
-        if (tb >= nblk) return;
+    if (LAYERS) {
         // tensors of the tile and of the at most 63 following symbols whose codewords complete its last word
-        const int64_t t_lo = t0;
-        int64_t t_hi = t_lo + CO3_PACK_SYMS + CO3_WAVE - 1;
+        int64_t t_hi = t0 + CO3_PACK_SYMS + CO3_WAVE - 1;
         t_hi = (t_hi < n ? t_hi : n) - 1;
-        const int s_lo = co3_find_seg(seg_off, nseg, t_lo), s_hi = co3_find_seg(seg_off, nseg, t_hi);
+        const int s_lo = co3_find_seg(seg_off, nseg, t0), s_hi = co3_find_seg(seg_off, nseg, t_hi);
         one_tensor = s_lo == s_hi;
         maxlen = 64u;                    // a mixed tile takes the general path
         if (one_tensor) {
             const Co3Code *cd = code_of(codes, s_lo);
+            wave_lds_sync();
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
                 const int q = lane + k * CO3_WAVE;
-                enc_all[wave * 256 + q] = q < K ? cd->enc[q] : 0ull;
+                enc_s[q] = q < K ? cd->enc[q] : 0ull;
             }
             maxlen = cd->maxlen;
             wave_lds_sync();
         }
     }
-    unsigned long long *stage = stage_all[wave];
 
     // packed (codeword << 6 | length) of symbol sy at element idx
     auto entry_at = [&](uint32_t sy, int64_t idx) -> uint64_t {
@@ -552,13 +694,12 @@ void k_enc_pack(const uint8_t *__restrict__ sym, int64_t n, int64_t stride, cons
     const uint32_t excl = incl - mybits;
     const uint32_t tilebits = (uint32_t)__builtin_amdgcn_readlane((int)incl, CO3_WAVE - 1);
 
-    const uint64_t B0 = group_base + tile_base;
     const uint64_t B1 = B0 + tilebits;
 
     // chunk index: stream position of every chunk that starts at this lane's first symbol
     // (chunk sizes are powers of two: a shift, not a 64-bit division that every lane of the wavefront would sit through)
     if (nvalid > 0 && (i & (int64_t)(chunk_syms - 1)) == 0)
-        chunk_bitoff[(int64_t)u * (nchunks + 1) + (i >> __builtin_ctz((unsigned)chunk_syms))] = B0 + excl;
+        chunk_off[i >> __builtin_ctz((unsigned)chunk_syms)] = B0 + excl;
     // beyond the capacity nothing is written (the scan pass has reported it); uniform over the wavefront
     if ((B1 + 63) / 64 > (uint64_t)cap_words || tilebits == 0) return;
 
@@ -655,6 +796,180 @@ void k_enc_pack(const uint8_t *__restrict__ sym, int64_t n, int64_t stride, cons
     }
 }
 
+// The user's codewords for the general path; called by all threads of the workgroup.  Returns the longest length.
+__device__ __forceinline__ uint32_t load_tile_tables(uint64_t *enc_s, uint64_t *penc_s, const Co3Code *cd, int K, bool nib)
+{
+    for (int j = threadIdx.x; j < 256; j += blockDim.x) {
+        enc_s[j] = j < K ? cd->enc[j] : 0ull;
+        if (nib) {
+            const int lo = j & 15, hi = j >> 4;
+            const uint64_t e0 = lo < K ? cd->enc[lo] : 0ull, e1 = hi < K ? cd->enc[hi] : 0ull;
+            const uint32_t l1 = (uint32_t)(e1 & 63u);
+            penc_s[j] = ((((e0 >> 6) << l1) | (e1 >> 6)) << 6) | (uint64_t)((uint32_t)(e0 & 63u) + l1);
+        }
+    }
+    return cd->maxlen;
+}
+
+// SCAN: groupoff holds the sizes of at most 64 groups as the sizes pass left them.  Every wavefront takes them with
+// one load (lane g: group g), beside those it makes anyway, and scans them in registers; `report`: the first one of a
+// user writes what the scan kernel would.  That saves the kernel (3.3 us and its place in a chain of small ones: one
+// user of 65,536 elements 53.9 -> 50.0 us a pass).  With up to 682 groups a form of this took 59 us against 51 and the
+// kernel's 5.  Returns the stream positions at which the groups up to each lane's end.
+__device__ __forceinline__ uint32_t scan_groups(uint32_t bits, int lane, bool report, uint64_t *total_bits_u, uint64_t *chunk_last,
+                                                int64_t cap_words, int32_t *status)
+{
+    const uint32_t upto = wave_scan_incl_u32(bits, lane);
+    if (report && lane == CO3_WAVE - 1) {      // the last lane holds the stream's length
+        *total_bits_u = upto;
+        *chunk_last = upto;
+        if (((uint64_t)upto + 63) / 64 > (uint64_t)cap_words) co3_raise(status, CO3_ECAP);
+    }
+    return upto;
+}
+
+template <bool LAYERS>
+struct TileLds {
+    uint64_t enc_all[LAYERS ? EN_WAVES * 256 : 256];
+    uint64_t penc_s[LAYERS ? 1 : 256];           // codeword pairs, symbols two per byte
+    unsigned long long stage_all[EN_WAVES][EN_STAGE_WORDS];
+};
+
+// A tile per wavefront.  LAYERS = false: one code per user (codes[u]), its table shared by the workgroup.  LAYERS = true:
+// one code per tensor shared by all users (codes[tensor]); each wavefront keeps the table of its tile's tensor.
+// The per-user form is compiled for eight wavefronts per SIMD (64 registers; a few spills on the rarely taken
+// paths): it is bound by the latency of its per-tile chain, and residency is what hides it.
+template <bool LAYERS, bool SCAN>
+__global__ __launch_bounds__(EN_BLOCK) __attribute__((amdgpu_waves_per_eu(LAYERS ? 5 : 8, LAYERS ? 5 : 8)))
+void k_enc_pack(const uint8_t *__restrict__ sym, int64_t n, int64_t stride, const void *__restrict__ codes, int K,
+                const int64_t *__restrict__ seg_off_g, int nseg, const uint64_t *__restrict__ tileoff, int64_t nblk,
+                const uint64_t *__restrict__ groupoff, int64_t ngrp, uint64_t *__restrict__ words, int64_t cap_words,
+                int chunk_syms, uint64_t *__restrict__ chunk_bitoff, int64_t nchunks, int sym_nib,
+                uint64_t *__restrict__ total_bits, int32_t *status)
+{
+    const int u = blockIdx.y;
+    const bool nib = !LAYERS && sym_nib != 0;
+    __shared__ TileLds<LAYERS> lds;
+    __shared__ int64_t seg_cache[LAYERS ? CO3_SEG_CACHE : 1];
+    const int lane = threadIdx.x & (CO3_WAVE - 1);
+    const int wave = threadIdx.x / CO3_WAVE;
+    const int64_t tb = (int64_t)blockIdx.x * EN_WAVES + wave;
+    // Everything the wavefront reads from memory apart from the tables is requested first, so that its latency
+    // and that of the table load below (with its barrier) overlap.
+    const bool live = tb < nblk;                     // uniform: the wavefront has a tile
+    uint32_t s[4], next_sym;
+    uint2 raw;
+    int nvalid;
+    bool has_next;
+    load_tile(sym + (int64_t)u * (nib ? stride / 2 : stride), nib, n, tb, lane, s, raw, nvalid, next_sym, has_next);
+    uint64_t group_base = 0;
+    uint32_t group_bits = 0;
+    if (SCAN) group_bits = lane < (int)ngrp ? (uint32_t)groupoff[(int64_t)u * ngrp + lane] : 0u;   // (64 groups fit 32 bits)
+    else if (live) group_base = groupoff[(int64_t)u * ngrp + tb / CO3_PACK_GROUP];
+    const uint64_t tile_base = live ? tileoff[(int64_t)u * nblk + tb] : 0ull;
+    uint64_t *chunk_off = chunk_bitoff + (int64_t)u * (nchunks + 1);
+
+    uint32_t maxlen = 0u;
+    const int64_t *seg_off = seg_off_g;
+    if (LAYERS) seg_off = co3_cache_segs(seg_off_g, nseg, seg_cache);
+    else maxlen = load_tile_tables(lds.enc_all, lds.penc_s, code_of(codes, u), K, nib);
+    __syncthreads();
+    if (tb >= nblk) return;
+    if (SCAN) {
+        const uint32_t upto = scan_groups(group_bits, lane, tb == 0, total_bits + u, chunk_off + nchunks, cap_words, status);
+        const int grp = __builtin_amdgcn_readfirstlane((int)(tb / CO3_PACK_GROUP));
+        group_base = grp ? (uint32_t)__builtin_amdgcn_readlane((int)upto, grp - 1) : 0u;
+    }
+    pack_tile<LAYERS>(s, raw, nvalid, next_sym, has_next, nib, n, codes, K, seg_off, nseg, tb, lane, lds.enc_all + (LAYERS ? wave * 256 : 0), lds.penc_s,
+                      lds.stage_all[wave], maxlen, group_base + tile_base, words + (int64_t)u * cap_words, cap_words, chunk_syms,
+                      chunk_off);
+}
+
+// `blocks` blocks of four tiles per workgroup (2 or 4, a group of tiles at most): together where they are whole and of one
+// code, else tile by tile.
+template <bool LAYERS, bool SCAN>
+__global__ __launch_bounds__(EN_BLOCK) __attribute__((amdgpu_waves_per_eu(LAYERS ? 5 : 8, LAYERS ? 5 : 8)))
+void k_enc_pack_blocks(const uint8_t *__restrict__ sym, int64_t n, int64_t stride, const void *__restrict__ codes, int K,
+                       const int64_t *__restrict__ seg_off_g, int nseg, const uint64_t *__restrict__ tileoff, int64_t nblk,
+                       const uint64_t *__restrict__ groupoff, int64_t ngrp, uint64_t *__restrict__ words, int64_t cap_words,
+                       int chunk_syms, uint64_t *__restrict__ chunk_bitoff, int64_t nchunks, int sym_nib,
+                       uint64_t *__restrict__ total_bits, int32_t *status, int blocks)
+{
+    const int u = blockIdx.y;
+    const bool nib = !LAYERS && sym_nib != 0;
+    __shared__ union {
+        PackLds wg;
+        TileLds<LAYERS> tile;
+    } lds;
+    __shared__ int64_t seg_cache[LAYERS ? CO3_SEG_CACHE : 1];
+    const int lane = threadIdx.x & (CO3_WAVE - 1);
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / CO3_WAVE);
+    static_assert(CO3_PACK_GROUP % EN_WAVES == 0, "the tiles of a workgroup lie in one group");
+    const int64_t tb0 = (int64_t)blockIdx.x * EN_WAVES * blocks;
+    const int64_t i0 = tb0 * CO3_PACK_SYMS, i_end = i0 + (int64_t)blocks * EN_WG_SYMS;
+    const int64_t grp = tb0 / CO3_PACK_GROUP;
+    const uint8_t *su = sym + (int64_t)u * (nib ? stride / 2 : stride);
+    uint64_t *wu = words + (int64_t)u * cap_words;
+    uint64_t *chunk_off = chunk_bitoff + (int64_t)u * (nchunks + 1);
+    const uint64_t *toff = tileoff + (int64_t)u * nblk + tb0;
+    // stream positions of the workgroup's group of tiles and of its end: requested here, made when needed
+    const bool ends_inside = (tb0 + EN_WAVES * blocks) % CO3_PACK_GROUP != 0 && tb0 + EN_WAVES * blocks < nblk;
+    const uint64_t end_off = ends_inside ? toff[EN_WAVES * blocks] : 0ull;
+    uint32_t group_bits = 0;
+    uint64_t group_off = 0, group_next = 0;
+    if (SCAN) group_bits = lane < (int)ngrp ? (uint32_t)groupoff[(int64_t)u * ngrp + lane] : 0u;   // (64 groups fit 32 bits)
+    else {
+        group_off = groupoff[(int64_t)u * ngrp + grp];
+        group_next = grp + 1 < ngrp ? groupoff[(int64_t)u * ngrp + grp + 1] : total_bits[u];
+    }
+    auto where = [&](uint64_t &group_base, uint64_t &end_bit) {
+        group_base = group_off;
+        uint64_t group_end = group_next;
+        if (SCAN) {
+            const uint32_t upto = scan_groups(group_bits, lane, tb0 + wave == 0, total_bits + u, chunk_off + nchunks, cap_words, status);
+            group_base = grp ? (uint32_t)__builtin_amdgcn_readlane((int)upto, (int)grp - 1) : 0u;
+            group_end = (uint32_t)__builtin_amdgcn_readlane((int)upto, (int)grp);
+        }
+        end_bit = ends_inside ? group_base + end_off : group_end;
+    };
+    const int64_t *seg_off = LAYERS ? co3_cache_segs(seg_off_g, nseg, seg_cache) : seg_off_g;
+
+    if (i_end <= n) {
+        // whole blocks; the codes of their symbols and of the at most 63 behind them that complete the last word
+        int code = u;
+        bool together = true;
+        if (LAYERS) {
+            const int64_t i_last = (i_end + CO3_WAVE - 1 < n ? i_end + CO3_WAVE - 1 : n) - 1;
+            code = __builtin_amdgcn_readfirstlane(co3_find_seg(seg_off, nseg, i0));
+            together = __builtin_amdgcn_readfirstlane(co3_find_seg(seg_off, nseg, i_last)) == code;
+        }
+        if (!together) {
+        } else if (nib) {
+            if (pack_blocks<true>(lds.wg, su, code_of(codes, code), K, n, i0, blocks, wave, lane, where, toff, wu, cap_words,
+                                  chunk_syms, chunk_off)) return;
+        } else if (pack_blocks<false>(lds.wg, su, code_of(codes, code), K, n, i0, blocks, wave, lane, where, toff, wu, cap_words,
+                                      chunk_syms, chunk_off)) return;
+    }
+
+    const uint32_t maxlen = LAYERS ? 0u : load_tile_tables(lds.tile.enc_all, lds.tile.penc_s, code_of(codes, u), K, nib);
+    __syncthreads();
+    uint64_t group_base, end_bit;
+    where(group_base, end_bit);
+#pragma unroll 1
+    for (int k = 0; k < blocks; ++k) {
+        const int64_t tb = tb0 + k * EN_WAVES + wave;
+        if (tb >= nblk) break;
+        uint32_t s[4], next_sym;
+        uint2 raw;
+        int nvalid;
+        bool has_next;
+        load_tile(su, nib, n, tb, lane, s, raw, nvalid, next_sym, has_next);
+        pack_tile<LAYERS>(s, raw, nvalid, next_sym, has_next, nib, n, codes, K, seg_off, nseg, tb, lane,
+                          lds.tile.enc_all + (LAYERS ? wave * 256 : 0), lds.tile.penc_s, lds.tile.stage_all[wave], maxlen,
+                          group_base + toff[k * EN_WAVES + wave], wu, cap_words, chunk_syms, chunk_off);
+    }
+}
+
 hipError_t co3_launch_enc_scan(uint64_t *sizes, int64_t nsizes, int U, int64_t cap_words, uint64_t *chunk_bitoff,
                                int64_t nchunks, uint64_t *total_bits, int32_t *status, hipStream_t st)
 {
@@ -662,6 +977,16 @@ hipError_t co3_launch_enc_scan(uint64_t *sizes, int64_t nsizes, int U, int64_t c
     hipLaunchKernelGGL(k_enc_scan, dim3(U), dim3(SC_BLOCK), 0, st, sizes, nsizes, cap_words, chunk_bitoff, nchunks,
                        total_bits, status);
     return hipGetLastError();
+}
+
+// Blocks of four tiles that a workgroup of the packer takes in a row; 1: a tile per wavefront.  Few workgroups end sooner
+// with little each: 16 blocks (one user of 65,536 elements) 4.4 | 5.9 | 7.0 us with 1 | 2 | 4, 302 blocks 5.3 | 7.9 | 7.9;
+// 2,728 (one user's ResNet-18) 10.6 | 10.3 | 10.7 and no gain in its pass; 10,916 (four users', shared codes) 50 | 35.0 |
+// 35.9; 27,280 (ten users, E3M0) 52 | 43.8 | 37.
+static int pack_blocks_per_workgroup(int64_t nblk, int U)
+{
+    const int64_t all = (nblk + EN_WAVES - 1) / EN_WAVES * U;
+    return all >= 16384 ? 4 : all >= 4096 ? 2 : 1;
 }
 
 // seg_off != NULL selects one code per tensor (codes[tensor], shared by the users) instead of codes[user]
@@ -690,20 +1015,21 @@ hipError_t co3_launch_encode(const uint8_t *sym, int64_t n, int U, int64_t strid
     if (!scan_in_pack && co3_launch_enc_scan(groupsum, ngrp, U, cap_words, chunk_bitoff, nchunks, total_bits, status, st) != hipSuccess)
         return hipGetLastError();
     if (nblk > 0) {
-        const unsigned gx = (unsigned)((nblk + EN_WAVES - 1) / EN_WAVES);
+        const int blocks = pack_blocks_per_workgroup(nblk, U);
+        const unsigned gx = (unsigned)((nblk + EN_WAVES * blocks - 1) / (EN_WAVES * blocks));
         Co3LaunchTimer tm(CO3_K_ENC_PACK, st);
-        if (seg_off)
-            hipLaunchKernelGGL((k_enc_pack<true, false>), dim3(gx, U), dim3(EN_BLOCK), 0, st, sym, n, stride, codes, K, seg_off,
-                               nseg, (const uint64_t *)tilesum, nblk, (const uint64_t *)groupsum, ngrp, words,
-                               cap_words, chunk_syms, chunk_bitoff, nchunks, 0, total_bits, status);
-        else if (scan_in_pack)
-            hipLaunchKernelGGL((k_enc_pack<false, true>), dim3(gx, U), dim3(EN_BLOCK), 0, st, sym, n, stride, codes, K, seg_off,
-                               nseg, (const uint64_t *)tilesum, nblk, (const uint64_t *)groupsum, ngrp, words,
-                               cap_words, chunk_syms, chunk_bitoff, nchunks, sym_nib, total_bits, status);
-        else
-            hipLaunchKernelGGL((k_enc_pack<false, false>), dim3(gx, U), dim3(EN_BLOCK), 0, st, sym, n, stride, codes, K, seg_off,
-                               nseg, (const uint64_t *)tilesum, nblk, (const uint64_t *)groupsum, ngrp, words,
-                               cap_words, chunk_syms, chunk_bitoff, nchunks, sym_nib, total_bits, status);
+#define CO3_PACK_LAUNCH(KERNEL, ...)                                                                                   \
+    hipLaunchKernelGGL(KERNEL, dim3(gx, U), dim3(EN_BLOCK), 0, st, sym, n, stride, codes, K, seg_off, nseg,             \
+                       (const uint64_t *)tilesum, nblk, (const uint64_t *)groupsum, ngrp, words, cap_words, chunk_syms, \
+                       chunk_bitoff, nchunks, sym_nib, total_bits, status __VA_OPT__(,) __VA_ARGS__)
+        if (blocks > 1) {
+            if (seg_off) CO3_PACK_LAUNCH((k_enc_pack_blocks<true, false>), blocks);
+            else if (scan_in_pack) CO3_PACK_LAUNCH((k_enc_pack_blocks<false, true>), blocks);
+            else CO3_PACK_LAUNCH((k_enc_pack_blocks<false, false>), blocks);
+        } else if (seg_off) CO3_PACK_LAUNCH((k_enc_pack<true, false>));
+        else if (scan_in_pack) CO3_PACK_LAUNCH((k_enc_pack<false, true>));
+        else CO3_PACK_LAUNCH((k_enc_pack<false, false>));
+#undef CO3_PACK_LAUNCH
     }
     return hipGetLastError();
 }
