@@ -3,6 +3,8 @@
 #include "co3_dev.h"
 #include "kernels.h"
 
+#include <type_traits>
+
 #define DE_BLOCK 512           // most lanes of a workgroup of k_decode
 #define DE_MIN_BLOCK 256       // load_tables wants this many threads
 
@@ -33,20 +35,27 @@ __device__ __forceinline__ const Co3Code *dcode_of(const void *codes, int u)
 #define DE_REFILL 4
 enum { DE_SHORT = 0, DE_LONG = 1, DE_PAIRS = 2, DE_RETRY = 3 };   // fast-path variants of decode_range
 
+// AHEAD = 0: the blocks that the next run may need are requested, up to two, 16 bytes at any place.
+// AHEAD = 4: 64 aligned bytes at a time, which wait in registers.  A full chip's lanes, each at a chunk of its own, have
+// more 128-byte lines open than its L2 holds, and every visit of a line may fetch it again: 16 x 25 M E4M3 (a stream of
+// 337 MB) read 1.18 GB in 306 us, now 1.01 GB in 281; a chip that is not full pays for the registers' shuffling (32 x
+// 1 M E3M1 29 | 31 us) and keeps to 0, as the two-symbol table does (10 x 11.2 M E3M0 49 | 52).  With 128 bytes at a
+// time the kernel took 305, with 32 291.
+template <int AHEAD>
 struct LaneStream {
-    const uint4 *blocks;   // the user's stream as 16-byte blocks
-    int64_t nblocks;       // blocks inside the buffer; beyond read as zeros
-    int64_t base_blk;      // absolute index of relative block 0 (the block holding the chunk start)
+    const uint4 *blocks;   // the user's stream from relative block 0 (the one that holds the chunk start) on, as 16-byte blocks
+    uint64_t base_bit;     // stream position of relative block 0
+    uint32_t nblocks;      // relative blocks inside the buffer; beyond read as zeros
+    uint32_t phase;        // AHEAD: position of relative block 0 in its aligned group of AHEAD blocks
     uint32_t *slot;        // this lane's ring in LDS
-    uint32_t rel;          // current bit position relative to block base_blk
+    uint32_t rel;          // current bit position relative to block 0
     uint32_t loaded;       // relative blocks [loaded-4, loaded) are in the ring
-    uint32_t nfly;         // blocks requested beyond `loaded`: fl0 holds block loaded, fl1 block loaded+1
-    uint4 fl0, fl1;
+    uint32_t have;         // blocks [loaded, loaded + have) are in ahead[] or on their way there
+    uint4 ahead[AHEAD ? AHEAD : 2];
 
     __device__ __forceinline__ uint4 fetch(uint32_t relblk) const
     {
-        int64_t b = base_blk + relblk;
-        return (b >= 0 && b < nblocks) ? blocks[b] : make_uint4(0u, 0u, 0u, 0u);
+        return relblk < nblocks ? blocks[relblk] : make_uint4(0u, 0u, 0u, 0u);
     }
     __device__ __forceinline__ void put(uint32_t relblk, uint4 v)
     {
@@ -57,28 +66,46 @@ struct LaneStream {
         slot[top * RING_ROW_DW] = v.y;
         if (top == 16u) slot[0] = v.y;
     }
+    // the next block into the ring (have > 0)
+    __device__ __forceinline__ void pop()
+    {
+        put(loaded, ahead[0]);
+#pragma unroll
+        for (int k = 0; k + 1 < (AHEAD ? AHEAD : 2); ++k) ahead[k] = ahead[k + 1];
+        ++loaded;
+        --have;
+    }
+    // AHEAD = 0: all that was requested into the ring
     __device__ __forceinline__ void land()
     {
-        if (nfly >= 1u) put(loaded, fl0);
-        if (nfly == 2u) put(loaded + 1u, fl1);
-        loaded += nfly;
-        nfly = 0;
+        if (have >= 1u) put(loaded, ahead[0]);
+        if (have == 2u) put(loaded + 1u, ahead[1]);
+        loaded += have;
+        have = 0;
     }
     // make pieces [.., need_dw) resident (synchronous; only used off the fast path).  Callers ask for
-    // at most block cur+2, so the block overwritten (loaded-4) always lies behind the position.
+    // at most block cur+3, so the block overwritten (loaded-4) always lies behind the position.
     __device__ __forceinline__ void ensure(uint32_t need_dw)
     {
-        land();
+        if (AHEAD == 0) land();
         while (loaded * 4u < need_dw) {
-            put(loaded, fetch(loaded));
-            ++loaded;
+            if (AHEAD && have) pop();
+            else {
+                put(loaded, fetch(loaded));
+                ++loaded;
+            }
         }
     }
-    __device__ __forceinline__ void open(uint64_t p0)
+    // words: the user's stream of cap_words 64-bit words, an even number
+    __device__ __forceinline__ void open(const uint64_t *words, int64_t cap_words, uint64_t p0)
     {
-        base_blk = (int64_t)(p0 >> 7);
+        const uint64_t b0 = p0 >> 7, all = (uint64_t)cap_words / 2;
+        blocks = reinterpret_cast<const uint4 *>(words) + b0;
+        nblocks = b0 < all ? (uint32_t)(all - b0 < 0xffffffffull ? all - b0 : 0xffffffffull) : 0u;
+        phase = AHEAD ? (uint32_t)(reinterpret_cast<uintptr_t>(blocks) >> 4) & (AHEAD - 1u) : 0u;
+        base_bit = b0 << 7;
         rel = (uint32_t)(p0 & 127u);
-        nfly = 0;
+        have = 0;
         uint4 a = fetch(0), b = fetch(1), c = fetch(2), d = fetch(3);
         put(0, a);
         put(1, b);
@@ -86,23 +113,47 @@ struct LaneStream {
         put(3, d);
         loaded = 4;
     }
-    // Start of a run of DE_GROUP symbols: what was requested at the previous boundary enters the ring,
-    // and up to two further blocks are requested so that four blocks from the current one on are
-    // resident or on their way.  The blocks they will replace lie behind the position.
+    // Start of a run of DE_GROUP symbols: what was requested at an earlier boundary enters the ring, so that it holds
+    // four blocks from the current one on (the blocks they replace lie behind the position), and more is requested.
     __device__ __forceinline__ void group_boundary()
     {
-        land();
         const uint32_t want = (rel >> 7) + 4u;
-        if (loaded < want) {
-            fl0 = fetch(loaded);
-            nfly = 1;
-            if (loaded + 1u < want) {
-                fl1 = fetch(loaded + 1u);
-                nfly = 2;
+        if (AHEAD == 0) {
+            land();
+            if (loaded < want) {
+                ahead[0] = fetch(loaded);
+                have = 1;
+                if (loaded + 1u < want) {
+                    ahead[1] = fetch(loaded + 1u);
+                    have = 2;
+                }
             }
+            return;
+        }
+        if (loaded < want && have) {
+            pop();
+            if (loaded < want && have) pop();
+        }
+        if (have == 0u) {
+            const uint32_t cnt = AHEAD - ((phase + loaded) & (AHEAD - 1u));
+            if (cnt == AHEAD && loaded + AHEAD <= nblocks) {
+#pragma unroll
+                for (int k = 0; k < AHEAD; ++k) ahead[k] = blocks[loaded + k];
+            } else {                               // the first group, the end of the buffer
+#pragma unroll
+                for (int k = 0; k < AHEAD; ++k)
+                    if ((uint32_t)k < cnt) ahead[k] = fetch(loaded + k);
+            }
+            have = cnt;
         }
     }
-    __device__ __forceinline__ uint64_t pos() const { return ((uint64_t)base_blk << 7) + rel; }
+    // what a stretch of long codewords needs and has been requested is waited for
+    __device__ __forceinline__ void hurry()
+    {
+        if (AHEAD == 0) land();
+        else ensure((((rel + 240u) >> 7) + 1u) * 4u);
+    }
+    __device__ __forceinline__ uint64_t pos() const { return base_bit + rel; }
     // the 32 stream bits at the current position
     __device__ __forceinline__ uint32_t peek32() const
     {
@@ -134,10 +185,19 @@ struct LaneStream {
 // blob stores a table of at most CO3_LUT_BITS_MAX bits; a workgroup that has LDS to spare widens it
 // (DE_WIDE_BITS) while loading, so that fewer codewords take the canonical search.
 #define DE_WIDE_BITS 14
-template <int BITS>
+// What the table leaves out lies above all it resolves (canonical codewords grow with their length): a second one,
+// indexed by the distance from there, resolves codewords of up to as many bits as ENTRIES2 entries reach, and no more
+// than are left of a window after the lookups since it was read.  It takes the place of a search over the lengths'
+// limits, five LDS reads one after the other: one user's ResNet-18 in E4M3 (some wavefronts miss at most symbols) 60 ->
+// 44 us, ten users' 119 -> 100, four users' under shared codes 105 -> 92.  Making it costs a workgroup a third of a
+// microsecond: chunks of less than 256 symbols do without (10 x 11.2 M in chunks of 64 95 | 101 us).
+template <int BITS, int ENTRIES2>
 struct DecTablesT {
-    static constexpr int kBits = BITS;
+    static constexpr int kBits = BITS, kEntries2 = ENTRIES2;
+    static constexpr int kBits2 = 64 - (DE_REFILL - 1) * BITS < 32 ? 64 - (DE_REFILL - 1) * BITS : 32;
     alignas(16) uint16_t lut[1 << BITS];
+    uint16_t lut2[ENTRIES2];
+    uint32_t from2, shift2, n2;   // entry (prefix of 32 bits - from2) >> shift2, below n2 (0: none)
     uint64_t first_code[65];
     uint16_t count[66];
     uint16_t base[66];
@@ -145,10 +205,12 @@ struct DecTablesT {
     uint64_t lim_incl[65];   // largest 64-bit window (codeword left-aligned, ones below) of a codeword of length <= l
     uint32_t maxlen, lut_bits;
 };
-typedef DecTablesT<CO3_LUT_BITS_MAX> DecTables;
+typedef DecTablesT<CO3_LUT_BITS_MAX, 8> DecTablesPairs;     // beside the two-symbol table
+typedef DecTablesT<CO3_LUT_BITS_MAX, 256> DecTables;      // shared per-layer codes: four of them a workgroup
 
+// second: whether the second table is made (the same for all threads).
 template <class Tables>
-__device__ __forceinline__ void load_tables(Tables &t, const Co3Code *cd)
+__device__ __forceinline__ void load_tables(Tables &t, const Co3Code *cd, bool second)
 {
     constexpr uint32_t BITS = Tables::kBits;
     const uint32_t lb = cd->lut_bits > CO3_LUT_BITS_MAX ? CO3_LUT_BITS_MAX : (cd->lut_bits < 1 ? 1 : cd->lut_bits);
@@ -205,6 +267,7 @@ __device__ __forceinline__ void load_tables(Tables &t, const Co3Code *cd)
             }
         }
     }
+    const bool make2 = second && ml > nb;
     __syncthreads();
     if (wide != 0u) {
         // the codewords of lengths lb+1 .. nb, a thread each, enter where their prefixes lie
@@ -215,11 +278,12 @@ __device__ __forceinline__ void load_tables(Tables &t, const Co3Code *cd)
                 if (code < (1ull << l))
                     for (uint32_t h = 0; h < (1u << (nb - l)); ++h) t.lut[((uint32_t)code << (nb - l)) + h] = e;
             }
-        __syncthreads();
     }
-    if (t.maxlen > t.lut_bits) {      // only codes with codewords beyond the table prefix use the limits
-        for (int l = threadIdx.x; l < 65; l += blockDim.x) {
-            int j = l < (int)t.maxlen ? l : (int)t.maxlen;
+    // (beside that, by the other end of the workgroup; the caller's barrier is the next)
+    const int xr = BITS > CO3_LUT_BITS_MAX ? (int)step - 1 - x : x;
+    if (ml > nb) {                    // only codes with codewords beyond the table prefix use the limits
+        for (int l = xr; l < 65; l += (int)step) {
+            int j = l < (int)ml ? l : (int)ml;
             while (j >= 1 && t.count[j] == 0) --j;     // canonical order: shorter codewords are numerically below
             uint64_t lim = 0;
             if (j >= 1) {
@@ -227,6 +291,38 @@ __device__ __forceinline__ void load_tables(Tables &t, const Co3Code *cd)
                 lim = j == 64 ? last : (last << (64 - j)) | ((~0ull) >> j);
             }
             t.lim_incl[l] = lim;
+        }
+    }
+    if (x == 0 && !make2) t.n2 = t.from2 = t.shift2 = 0u;
+    if (make2) {
+        const int lane = x & (CO3_WAVE - 1);
+        const uint64_t end_nb = t.first_code[nb] + t.count[nb];          // uniform
+        const uint64_t left = (1ull << nb) - end_nb;                     // prefixes of nb bits that are left out
+        uint32_t top = nb;
+        while (top < ml && top < (uint32_t)Tables::kBits2 && (left << (top + 1u - nb)) <= (uint64_t)Tables::kEntries2) ++top;
+        const bool some = end_nb < (1ull << nb) && top > nb;             // (also of a damaged blob: within the array)
+        const uint32_t n2 = some ? (uint32_t)left << (top - nb) : 0u;
+        if (x == 0) {
+            t.from2 = some ? (uint32_t)end_nb << (32u - nb) : 0u;
+            t.shift2 = 32u - top;
+            t.n2 = n2;
+        }
+        if (some) {
+            // of every length the end of its range, as prefixes of `top` bits: lane l holds that of length l
+            const bool mid = lane > (int)nb && lane <= (int)top;
+            const uint64_t end = mid ? (t.first_code[lane] + t.count[lane]) << (top - lane) : 0ull;
+            const uint64_t from = end_nb << (top - nb);
+            const uint32_t mine = end < from ? 0u : end - from > 0xffffull ? 0xffffu : (uint32_t)(end - from);
+            for (uint32_t i = (uint32_t)xr; i < n2; i += step) {
+                uint32_t l = nb + 1u;
+                for (uint32_t k = nb + 1u; k <= top; ++k) l += i >= (uint32_t)__builtin_amdgcn_readlane((int)mine, (int)k) ? 1u : 0u;
+                uint32_t e = DE_MISS_LEN << 8;
+                if (l <= top) {
+                    const uint64_t off = ((from + i) >> (top - l)) - t.first_code[l];
+                    if (off < (uint64_t)t.count[l]) e = (l << 8) | t.sorted[(t.base[l] + (uint32_t)off) & 255u];
+                }
+                t.lut2[i] = (uint16_t)e;
+            }
         }
     }
 }
@@ -241,7 +337,7 @@ __device__ __forceinline__ void load_tables(Tables &t, const Co3Code *cd)
 // The second codeword is looked up with the bits after the first one, zero-filled: a codeword that
 // ends inside the prefix is determined by its own bits alone (prefix-free code).
 template <bool NIB>
-__device__ __forceinline__ void build_pairs(const DecTables &t, uint32_t *pairs)
+__device__ __forceinline__ void build_pairs(const DecTablesPairs &t, uint32_t *pairs)
 {
     const uint32_t down = DE_PAIR_BITS - t.lut_bits;
     for (uint32_t i = threadIdx.x; i < (1u << DE_PAIR_BITS); i += blockDim.x) {
@@ -278,8 +374,8 @@ __device__ __forceinline__ int decode_long(const Tables &t, uint64_t window, uin
 // Careful decoding of `count` <= 16 symbols (any codeword length, any stream content): used for runs
 // that the fast path could not vouch for and for the ragged end of a chunk.  Leaves blocks
 // cur .. cur+2 resident.  Symbols are returned 4 per word, first in the lowest byte.
-template <class Tables>
-__device__ __forceinline__ void decode_run_careful(const Tables &t, LaneStream &ls, int shift, int count, bool &ok,
+template <class Tables, class Stream>
+__device__ __forceinline__ void decode_run_careful(const Tables &t, Stream &ls, int shift, int count, bool &ok,
                                                    uint32_t w[4])
 {
     w[0] = w[1] = w[2] = w[3] = 0;
@@ -309,8 +405,8 @@ __device__ __forceinline__ void decode_run_careful(const Tables &t, LaneStream &
 // every DE_REFILL lookups (of at most DE_PAIR_BITS bits each).  An entry that holds only its first codeword is
 // completed from a lookup of its own, in a branch that the wavefront skips when no lane needs it and that leaves
 // a whole window behind.  mw: the last position at which the ring was read.
-template <bool NIB>
-__device__ __forceinline__ uint32_t pair_step(const LaneStream &ls, const uint32_t *pairs, uint64_t &win, uint32_t &m,
+template <bool NIB, class Stream>
+__device__ __forceinline__ uint32_t pair_step(const Stream &ls, const uint32_t *pairs, uint64_t &win, uint32_t &m,
                                               uint32_t &mw, bool &bad)
 {
     uint32_t e = pairs[win >> (64 - DE_PAIR_BITS)];
@@ -350,7 +446,7 @@ __device__ __forceinline__ uint32_t pair_step(const LaneStream &ls, const uint32
 // every window it read must lie inside the blocks that were resident when the run started, and
 // every window must have started a codeword.  Otherwise the run is decoded again by the careful
 // path from the saved position.  Codewords longer than the table prefix are resolved by a
-// canonical search (the lengths' upper limits are ordered), in a branch the wavefront skips when
+// second table or a canonical search (the lengths' upper limits are ordered), in a branch the wavefront skips when
 // no lane needs it: in place, symbol by symbol (DE_LONG), or after every four symbols (DE_RETRY).
 //
 // DE_SHORT is the instance for codes whose longest codeword fits the table prefix: there a miss can
@@ -360,8 +456,8 @@ __device__ __forceinline__ uint32_t pair_step(const LaneStream &ls, const uint32
 // boundary cover the symbols up to the next one); a lookup whose prefix does not hold both codewords
 // takes the second one from a lookup of its own (in a branch the wavefront skips when no lane needs
 // it), and a codeword longer than the prefix sends the run to the careful path.
-template <int MODE, class Tables>
-__device__ __forceinline__ void decode_range(const Tables &t, LaneStream &ls, int i0, int i1, uint8_t *out,
+template <int MODE, class Tables, class Stream>
+__device__ __forceinline__ void decode_range(const Tables &t, Stream &ls, int i0, int i1, uint8_t *out,
                                              int64_t run_step, bool &ok, const uint32_t *pairs = nullptr)
 {
     static_assert(DE_REFILL * Tables::kBits <= 64 && DE_REFILL == 4, "a window holds the lookups between two refills");
@@ -413,7 +509,7 @@ __device__ __forceinline__ void decode_range(const Tables &t, LaneStream &ls, in
         ls.group_boundary();
         // a stretch of long codewords (the last run took more than nine bits a symbol): what has just been
         // requested is waited for, which costs less than a run by the careful path
-        if (MODE != DE_PAIRS && ls.rel + 240u > ls.loaded * 128u) ls.land();
+        if (MODE != DE_PAIRS && ls.rel + 240u > ls.loaded * 128u) ls.hurry();
         const uint32_t rel0 = ls.rel;
         uint32_t w[4] = {0u, 0u, 0u, 0u};
         // Work with the negated position m = -rel.  The next 64 stream bits wait in registers and are read anew
@@ -430,11 +526,17 @@ __device__ __forceinline__ void decode_range(const Tables &t, LaneStream &ls, in
                 w[b >> 1] = __builtin_amdgcn_alignbit(e, w[b >> 1], 16);
             }
         } else {
-        // Codeword longer than the table prefix: the first length whose largest left-aligned codeword is not
-        // below the window.  (The limits do not decrease with the length and stay put beyond the longest
-        // codeword, so counting the limits below the window gives the length; nearly all long codewords end
-        // within four bits of the prefix: those limits are compared without a loop.)
-        auto search = [&](uint64_t w64) -> uint32_t {
+        // Codeword longer than the table prefix, at the start of the window w64: mostly from the second table.  Else the
+        // first length whose largest left-aligned codeword is not below the window.  (The limits do not decrease with
+        // the length and stay put beyond the longest codeword, so counting the limits below the window gives the
+        // length; without the second table nearly all end within four bits of the prefix, compared without a loop.)  `again`: the window is not known to hold all of it and is read anew for that.
+        auto search = [&](uint64_t &w64, bool again) -> uint32_t {
+            const uint32_t i2 = ((uint32_t)(w64 >> 32) - t.from2) >> t.shift2;
+            if (i2 < t.n2) {
+                const uint32_t e2 = t.lut2[i2];
+                if ((e2 >> 8) != DE_MISS_LEN) return e2;
+            }
+            if (again) w64 = ls.window64(mw = m);
             const uint32_t l0 = t.lut_bits + 1u;
             uint32_t l = l0;
 #pragma unroll
@@ -448,10 +550,9 @@ __device__ __forceinline__ void decode_range(const Tables &t, LaneStream &ls, in
         };
         // DE_RETRY tests for misses once per DE_REFILL symbols, after which the lane goes on one by one from the
         // first; DE_LONG tests at every symbol, and each lookup has to wait for the test of the last.  With the wide
-        // table a miss is rare in data that the code was made for (about one in 10^4 symbols of an 8-bit format):
-        // DE_LONG | DE_RETRY 16 x 25 M E4M3 423 | 408 us with the average, 32 x 1 M E3M1 60 | 52; but one user's 62
-        // tensors in E4M3, some with stretches of long codewords, 70 | 78.  With the narrow table (one miss in 200
-        // symbols) it is DE_LONG.
+        // table a miss is rare in data that the code was made for (about one in 2,000 symbols of an 8-bit format):
+        // DE_LONG | DE_RETRY 16 x 25 M E4M3 306 | 284 us, 32 x 1 M E3M1 38 | 32; but one user's 62 tensors in E4M3, some
+        // with stretches of long codewords, 44 | 54.  With the narrow table (one miss in 200 symbols) it is DE_LONG.
 #pragma unroll
         for (int q = 0; q < DE_GROUP / DE_REFILL; ++q) {
             win = ls.window64(mw = m);
@@ -461,10 +562,15 @@ __device__ __forceinline__ void decode_range(const Tables &t, LaneStream &ls, in
                 uint32_t e = t.lut[(uint32_t)(win >> 32) >> shift];
                 uint32_t drop = e >> 8;
                 if (MODE == DE_LONG && drop == DE_MISS_LEN) {   // skipped by the wavefront when no lane is here
-                    e = search(ls.window64(m));
-                    drop = 0u;
-                    mw = m - (e >> 8);
-                    win = ls.window64(mw);
+                    if (mw - m > 64u - Tables::kBits2) win = ls.window64(mw = m);
+                    e = search(win, true);
+                    drop = e >> 8;
+                    // the window is read anew where what is left of it may not hold the lookups to come
+                    if (b + 1 < DE_REFILL && mw - (m - drop) + (DE_REFILL - 1 - b) * Tables::kBits > 64u) {
+                        mw = m - drop;
+                        win = ls.window64(mw);
+                        drop = 0u;
+                    }
                 }
                 es[b] = e;
                 any |= e;
@@ -485,8 +591,10 @@ __device__ __forceinline__ void decode_range(const Tables &t, LaneStream &ls, in
 #pragma unroll 1
                 for (;;) {
                     if ((e >> 8) == DE_MISS_LEN) {     // (hits since the last read have left win short of bits)
-                        e = search(ls.window64(m));
-                        win = ls.window64(mw = m - (e >> 8));
+                        win = ls.window64(mw = m);
+                        e = search(win, false);
+                        if ((e >> 8) > (uint32_t)Tables::kBits2) win = ls.window64(mw = m - (e >> 8));
+                        else win <<= e >> 8;
                     } else {
                         win <<= (e >> 8) & 63u;
                     }
@@ -514,7 +622,7 @@ __device__ __forceinline__ void decode_range(const Tables &t, LaneStream &ls, in
 // workspace: two symbols per byte (the earlier one in the low half), 32 symbols per 16-byte store, run r
 // of 32 symbols at out + r * run_step.  One refill point per 32 symbols: with at most four bits per
 // symbol on average the blocks requested at one boundary cover the symbols up to the next one.
-__device__ __forceinline__ void decode_chunk_packed(const DecTables &t, LaneStream &ls, int nsym, uint8_t *out,
+__device__ __forceinline__ void decode_chunk_packed(const DecTablesPairs &t, LaneStream<0> &ls, int nsym, uint8_t *out,
                                                     int64_t run_step, bool &ok, const uint32_t *pairs)
 {
     const int shift = 32 - (int)t.lut_bits;
@@ -566,7 +674,7 @@ __device__ __forceinline__ void decode_chunk_packed(const DecTables &t, LaneStre
 // PAIRS: the workgroup also builds the two-symbol table (launched for alphabets of at most 16
 // symbols and chunks of at least 32); with TILED the workspace then holds two symbols per byte,
 // [U][tiles][chunk_syms/32][64 lanes][32 symbols in 16 bytes].
-template <bool TILED, bool PAIRS>
+template <bool TILED, bool PAIRS, int AHEAD>
 __global__ __launch_bounds__(DE_BLOCK) void k_decode(const uint64_t *__restrict__ words, int64_t cap_words,
                                                       const uint64_t *__restrict__ chunk_bitoff, int chunk_syms,
                                                       int64_t nchunks, int chunks_per_block, const void *__restrict__ codes,
@@ -577,7 +685,7 @@ __global__ __launch_bounds__(DE_BLOCK) void k_decode(const uint64_t *__restrict_
     // tables first: their LDS offsets then fit the immediate field of the read instructions
     __shared__ struct {
         uint32_t pairs[PAIRS ? (1 << DE_PAIR_BITS) : 1];
-        DecTablesT<PAIRS ? CO3_LUT_BITS_MAX : DE_WIDE_BITS> t;   // one symbol per lookup: the widened table
+        typename std::conditional<PAIRS, DecTablesPairs, DecTablesT<DE_WIDE_BITS, 256>>::type t;   // one symbol per lookup: the widened table
     } lds;
     extern __shared__ __align__(256) uint32_t ring[];   // chunks_per_block * RING_ROWS
     auto &t = lds.t;
@@ -588,13 +696,14 @@ __global__ __launch_bounds__(DE_BLOCK) void k_decode(const uint64_t *__restrict_
     const int64_t c = (int64_t)blockIdx.x * chunks_per_block + threadIdx.x;
     const bool active = (int)threadIdx.x < chunks_per_block && c < nchunks;   // further wavefronts load tables only
     const uint64_t *off = chunk_bitoff + (int64_t)u * (nchunks + 1);
-    const uint64_t p0 = active ? off[c] : 0, p1 = active ? off[c + 1] : 0;
-    LaneStream ls;
-    ls.blocks = reinterpret_cast<const uint4 *>(words + (int64_t)u * cap_words);
-    ls.nblocks = cap_words / 2;
+    const uint64_t p0 = active ? off[c] : 0, p1 = active ? off[c + 1] : 0, all_bits = off[nchunks];
+    LaneStream<AHEAD> ls;
     ls.slot = ring + (threadIdx.x / CO3_WAVE) * (RING_ROWS * RING_ROW_DW) + (threadIdx.x & (CO3_WAVE - 1));
-    if (active) ls.open(p0);
-    load_tables(t, dcode_of(codes, code_per_user ? u : 0));        // else one code shared by all users
+    if (active) ls.open(words + (int64_t)u * cap_words, cap_words, p0);
+    const int64_t first = c * chunk_syms;
+    const int nsym = active ? (int)(n - first < chunk_syms ? n - first : chunk_syms) : 0;
+    const bool second = !PAIRS && chunk_syms >= 256;
+    load_tables(t, dcode_of(codes, code_per_user ? u : 0), second);        // else one code shared by all users
     __syncthreads();
     if constexpr (PAIRS) {
         build_pairs<TILED>(t, pairs);
@@ -602,8 +711,6 @@ __global__ __launch_bounds__(DE_BLOCK) void k_decode(const uint64_t *__restrict_
     }
     if (!active) return;
 
-    int64_t first = c * chunk_syms;
-    int nsym = (int)(n - first < chunk_syms ? n - first : chunk_syms);
     uint8_t *out;
     int64_t run_step;
     if (TILED) {
@@ -614,17 +721,22 @@ __global__ __launch_bounds__(DE_BLOCK) void k_decode(const uint64_t *__restrict_
         out = sym_out + (int64_t)u * stride + first;
         run_step = 16;
     }
+    // Whether the wavefront looks for codewords beyond the table at every symbol: where one of its chunks takes more than
+    // eight bits a symbol, or half a bit a symbol more than the stream on average (chunks of 512: a third).  Chunks of
+    // data that the code was made for scatter by a tenth to an eighth of a bit (256 symbols); those of tensors that it
+    // was not made for lie beyond: one user's ResNet-18 in E4M3 44 us; with a line of 0.63 bits 53, of eight bits a
+    // symbol alone 54; 10 x 11.2 M E5M2 of one law 98 | 99 | 96.  Smaller chunks scatter more and keep to eight bits.
+    auto dense = [&]() -> bool {
+        float line = 8.0f;
+        if (second) line = fminf(line, (float)all_bits / (float)n + 8.0f * rsqrtf((float)chunk_syms));
+        return __any((float)(p1 - p0) > (float)nsym * line) != 0;
+    };
     bool ok = true;
     if constexpr (PAIRS && TILED) decode_chunk_packed(t, ls, nsym, out, run_step, ok, pairs);
     else if constexpr (PAIRS) decode_range<DE_PAIRS>(t, ls, 0, nsym, out, run_step, ok, pairs);
-    // (More than eight bits a symbol: the code does not fit these symbols, and most of them lie beyond the table.
-    // Four users of 11.2 M in E4M3, 1 % | 20 % of them in stretches of 4,096 such: DE_LONG 789 | 803 us, DE_RETRY 839 |
-    // 838.  Matched data stay below 7.7 bits in chunks of 256 and 8.2 of 64; a line at 7.25 would serve one user's
-    // ResNet-18, 70 us for 78, and cost E4M3 of shape 0.5, at 7.19 bits by itself, 121 for 115.)
     else if (t.maxlen <= t.lut_bits) decode_range<DE_SHORT>(t, ls, 0, nsym, out, run_step, ok);
-    else if (__any(p1 - p0 > (uint64_t)nsym * 8)) decode_range<DE_LONG>(t, ls, 0, nsym, out, run_step, ok);
+    else if (dense()) decode_range<DE_LONG>(t, ls, 0, nsym, out, run_step, ok);
     else decode_range<DE_RETRY>(t, ls, 0, nsym, out, run_step, ok);
-    ls.land();
     if (!(ok && ls.pos() == p1)) co3_raise(status, CO3_EBADSTREAM);
 }
 
@@ -638,9 +750,10 @@ __global__ __launch_bounds__(DE_BLOCK) void k_decode(const uint64_t *__restrict_
 // (512 chunks) are better given a code together with a neighbour.
 #define DL_BLOCK 512
 #define DL_SLOTS 4
+#define DL_AHEAD 4
 
 template <bool TILED>
-__global__ __launch_bounds__(DL_BLOCK) void k_decode_layers(const uint64_t *__restrict__ words, int64_t cap_words,
+__global__ __launch_bounds__(DL_BLOCK) __attribute__((amdgpu_waves_per_eu(4))) void k_decode_layers(const uint64_t *__restrict__ words, int64_t cap_words,
                                                              const uint64_t *__restrict__ chunk_bitoff, int chunk_syms,
                                                              int64_t nchunks, const void *__restrict__ codes,
                                                              const int64_t *__restrict__ seg_off, int nseg, int64_t n,
@@ -658,9 +771,7 @@ __global__ __launch_bounds__(DL_BLOCK) void k_decode_layers(const uint64_t *__re
     const int64_t c = (int64_t)blockIdx.x * DL_BLOCK + threadIdx.x;
     const bool active = c < nchunks;
     const uint64_t *off = chunk_bitoff + (int64_t)u * (nchunks + 1);
-    LaneStream ls;
-    ls.blocks = reinterpret_cast<const uint4 *>(words + (int64_t)u * cap_words);
-    ls.nblocks = cap_words / 2;
+    LaneStream<DL_AHEAD> ls;
     ls.slot = ring + (threadIdx.x / CO3_WAVE) * (RING_ROWS * RING_ROW_DW) + (threadIdx.x & (CO3_WAVE - 1));
     const int64_t first = c * chunk_syms;
     const int nsym = active ? (int)(n - first < chunk_syms ? n - first : chunk_syms) : 0;
@@ -682,15 +793,15 @@ __global__ __launch_bounds__(DL_BLOCK) void k_decode_layers(const uint64_t *__re
     bool ok = true;
     int cur = 0;                                                        // next symbol of the chunk to decode
     int cur_seg = nsym > 0 ? co3_find_seg(seg_off, nseg, first) : -1;   // the tensor that holds it
-    if (nsym > 0) ls.open(off[c]);
+    if (nsym > 0) ls.open(words + (int64_t)u * cap_words, cap_words, off[c]);
     for (int sg = b_lo; sg <= b_hi; ++sg) {
         __syncthreads();                 // nobody reads the slot that is replaced any more
         if (sg == b_lo) {
             for (int k = 0; k < DL_SLOTS - 1 && sg + k <= b_hi; ++k)
-                load_tables(t[(sg + k) & (DL_SLOTS - 1)], dcode_of(codes, sg + k));
+                load_tables(t[(sg + k) & (DL_SLOTS - 1)], dcode_of(codes, sg + k), true);
         }
         if (sg + DL_SLOTS - 1 <= b_hi)
-            load_tables(t[(sg + DL_SLOTS - 1) & (DL_SLOTS - 1)], dcode_of(codes, sg + DL_SLOTS - 1));
+            load_tables(t[(sg + DL_SLOTS - 1) & (DL_SLOTS - 1)], dcode_of(codes, sg + DL_SLOTS - 1), true);
         __syncthreads();
         bool any_long = false;           // uniform
         for (int k = 0; k < DL_SLOTS; ++k) any_long |= t[k].maxlen > t[k].lut_bits;
@@ -709,7 +820,6 @@ __global__ __launch_bounds__(DL_BLOCK) void k_decode_layers(const uint64_t *__re
         }
     }
     if (nsym > 0) {
-        ls.land();
         ok = ok && cur == nsym && ls.pos() == off[c + 1];
     }
     if (!ok) co3_raise(status, CO3_EBADSTREAM);
@@ -928,9 +1038,12 @@ hipError_t co3_launch_decode(const uint64_t *words, int64_t cap_words, const uin
     if (nchunks <= 0) return hipSuccess;
     const int per_block = decode_chunks_per_block(nchunks, U);
     const unsigned blocks = (unsigned)((nchunks + per_block - 1) / per_block);
+    // 64 bytes at a time (LaneStream): where the chunks fill the chip more than once and a lane's lie a line or more apart
+    const int known = co3_device_cus(), cus = known > 0 ? known : 256;
+    const bool wide_requests = chunk_syms >= 256 && (nchunks + CO3_WAVE - 1) / CO3_WAVE * U >= 20 * (int64_t)cus;
     const unsigned lblocks = (unsigned)((nchunks + DL_BLOCK - 1) / DL_BLOCK);
-#define CO3_DECODE_LAUNCH(T, P)                                                                                    \
-    hipLaunchKernelGGL((k_decode<T, P>), dim3(blocks, U), dim3(decode_lanes(per_block, P)),                        \
+#define CO3_DECODE_LAUNCH(T, P, A)                                                                                 \
+    hipLaunchKernelGGL((k_decode<T, P, A>), dim3(blocks, U), dim3(decode_lanes(per_block, P)),                        \
                        (size_t)per_block * RING_ROWS * sizeof(uint32_t), st, words, cap_words, chunk_bitoff, chunk_syms, \
                        nchunks, per_block, codes, code_per_user, n, sym_out, stride, status)
     Co3LaunchTimer tm(CO3_K_DECODE, st);
@@ -944,11 +1057,14 @@ hipError_t co3_launch_decode(const uint64_t *words, int64_t cap_words, const uin
         hipLaunchKernelGGL(k_decode_layers<false>, dim3(lblocks, U), dim3(DL_BLOCK), 0, st, words, cap_words,
                            chunk_bitoff, chunk_syms, nchunks, codes, seg_off, nseg, n, sym_out, stride, status);
     else if (co3_ws_packed(K, chunk_syms, 0)) {
-        if (tiled) CO3_DECODE_LAUNCH(true, true);
-        else CO3_DECODE_LAUNCH(false, true);
+        if (tiled) CO3_DECODE_LAUNCH(true, true, 0);
+        else CO3_DECODE_LAUNCH(false, true, 0);
+    } else if (wide_requests) {
+        if (tiled) CO3_DECODE_LAUNCH(true, false, 4);
+        else CO3_DECODE_LAUNCH(false, false, 4);
     } else {
-        if (tiled) CO3_DECODE_LAUNCH(true, false);
-        else CO3_DECODE_LAUNCH(false, false);
+        if (tiled) CO3_DECODE_LAUNCH(true, false, 0);
+        else CO3_DECODE_LAUNCH(false, false, 0);
     }
 #undef CO3_DECODE_LAUNCH
     return hipGetLastError();

@@ -46,6 +46,35 @@ def test_stretches_of_long_codewords(co3, E, M, n, C, U):
     assert torch.equal(pipe.sym_dec[:, :n], s)
 
 
+# more chunks than 20 wavefronts a compute unit hold: the stream is requested 64 aligned bytes at a time; every user's
+# begins at another place within these, and ends where the buffer does
+@pytest.mark.parametrize("E,M", [(4, 3), (3, 1)])
+@pytest.mark.parametrize("n,C,U", [(2_199_999, 256, 40), (24_000_257, 512, 7)])
+def test_requests_of_64_bytes(co3, E, M, n, C, U):
+    fmt = co3.Fmt(E, M)
+    K = fmt.K
+    p = np.maximum(0.9 ** np.arange(K), 1e-9)
+    w = np.maximum((p / p.sum() * 3e9), 1).astype(np.uint64).astype(np.uint32)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(n)
+    edges = torch.tensor(np.cumsum(p / p.sum()), device="cuda", dtype=torch.float32)
+    s = torch.empty((U, n), dtype=torch.uint8, device="cuda")
+    for u in range(U):
+        x = torch.bucketize(torch.rand(n, device="cuda", generator=gen), edges).clamp_(max=K - 1)
+        rare = torch.randint(K - 8, K, (n,), device="cuda", generator=gen)
+        at = (torch.rand((n + 39) // 40, device="cuda", generator=gen) < 0.01).repeat_interleave(40)[:n]
+        s[u] = torch.where(at, rare, x).to(torch.uint8)
+    pipe = co3.Co3Pipeline(U, n, fmt, chunk_syms=C, cap_words=(n // 6) // 8 * 8 + 2)
+    pipe.sym[:, :n] = s
+    pipe.build(torch.from_numpy(np.tile(w.view(np.int32), (U, 1))).cuda())
+    pipe.encode()
+    longest = (int(pipe.total_bits.max()) + 127) // 128 * 2          # as little room as the streams leave
+    pipe.words = pipe.words[:, :longest + (6 if longest % 8 == 0 else 0)].contiguous()
+    pipe.decode()
+    assert pipe.poll() == 0
+    assert torch.equal(pipe.sym_dec[:, :n], s)
+
+
 def fibonacci(k):
     w = [1, 1]
     while len(w) < k:
