@@ -838,13 +838,15 @@ __global__ __launch_bounds__(DL_BLOCK) __attribute__((amdgpu_waves_per_eu(4))) v
 // its K/2 magnitudes of every user from LDS as TABLE = 2 does (U * K/2 values computed for 4096 * U symbols;
 // 16 users of 11.2 M elements in 62 tensors, E4M3: 113 -> 76 us); the other steps look up a tensor per run or element.
 //
-// Bound by latency and, with many users, by issue: how many wavefronts a SIMD holds counts.  They are set by the
-// runs that straddle tensors, though few do: with an address per element kept from user to user, and the 64-bit
-// comparisons that found its tensor, the kernel took 227 to 230 registers (NIB) and 132 to 135; now 128 to 132 and
-// 82 to 86.  Average of 11.2 M elements in 62 tensors, before | now: E3M0 two users 32 | 29 us, ten 70 | 55; E4M3
-// two 27 | 24, three 36 | 28, ten 69 | 54.  In 33,333 tensors of three: E3M0 ten users 51 | 50.
-template <int TABLE, bool NIB>
-__global__ __launch_bounds__(PT_WAVES(NIB) * CO3_WAVE) __attribute__((amdgpu_waves_per_eu(NIB ? 3 : 4)))
+// Bound by latency and, with many users, by issue: how many wavefronts a SIMD holds counts, and how many users' symbols
+// are on their way at once (PT_AHEAD).  Registers are set by the runs that straddle tensors, though few do: an address
+// per element kept from user to user, and 64-bit comparisons to find its tensor, had brought them to 227.  One user's
+// symbols at a time | as now: one tensor, 32 users of 1 M E3M1 23 | 15.4 us, 16 of 25 M E4M3 121 | 101, 10 of 11.2 M E3M0
+// 28.4 | 27.4; 62 tensors of 11.2 M elements in E4M3, one user 21 | 16.7, two 26.7 | 19.2, four 29 | 24, ten 55 | 45.6; six
+// in E3M0 38 | 30.
+template <int TABLE, bool NIB, int PT_AHEAD>
+__global__ __launch_bounds__(PT_WAVES(NIB) * CO3_WAVE)
+__attribute__((amdgpu_waves_per_eu(TABLE == 1 || TABLE == 2 ? (NIB ? 4 : PT_AHEAD == 1 ? 7 : 5) : (NIB ? 3 : 4))))
 void k_ps_sum_tiled(const uint8_t *__restrict__ symt, int64_t n, int U, int64_t ws_stride, int chunk_syms, int64_t nruns,
                     const int32_t *__restrict__ anchor, const float *__restrict__ scale,
                     const int64_t *__restrict__ seg_off_g, int nseg, co3_fmt fmt, const float *acc_in, float divisor,
@@ -856,6 +858,8 @@ void k_ps_sum_tiled(const uint8_t *__restrict__ symt, int64_t n, int U, int64_t 
     const int EM = fc.E + fc.M, M = fc.M, F = fc.F;
     const uint32_t cmask = (uint32_t)fc.codemax;
     const int runs_per_chunk = chunk_syms / EPT;
+    const float recip = divisor > 0.f ? 1.0f / divisor : 0.f;
+    const bool pow2 = (__float_as_uint(divisor) & 0x7fffffu) == 0u;      // (a whole number below 2^31)
     // value of symbol s of user u in tensor sg; with multipliers (scale != NULL) the level is divided by
     // the user's multiplier, one fp32 rounding
     auto value = [&](uint32_t s, int u, int sg) -> float {
@@ -869,16 +873,14 @@ void k_ps_sum_tiled(const uint8_t *__restrict__ symt, int64_t n, int U, int64_t 
         return NIB ? (w[k >> 3] >> (4 * (k & 7))) & 0xfu : (w[k >> 2] >> (8 * (k & 3))) & 0xffu;
     };
     constexpr bool ONE = TABLE == 1 || TABLE == 2;               // one tensor, nothing to look up
+    constexpr bool HALF = TABLE == 2 || TABLE == 3;              // the magnitudes alone
     __shared__ int64_t seg_cache[ONE ? 1 : CO3_SEG_CACHE];
     const int64_t *seg_off = ONE ? seg_off_g : co3_cache_segs(seg_off_g, nseg, seg_cache);
     extern __shared__ float value_of[];    // [U][K] or [U][K/2], TABLE only
     int table_seg = -1;                    // TABLE 3: the tensor whose values are there
     if (ONE) {
-        const int H = TABLE == 1 ? fc.K : fc.K >> 1;
-        for (int j = threadIdx.x; j < U * H; j += PT_BLOCK) {
-            const int u = j / H;
-            value_of[j] = value((uint32_t)(j - u * H), u, 0);
-        }
+        const int sh = EM + (HALF ? 0 : 1);                    // (K is a power of two)
+        for (int j = threadIdx.x; j < U << sh; j += PT_BLOCK) value_of[j] = value((uint32_t)j & ((1u << sh) - 1u), j >> sh, 0);
         __syncthreads();
     }
     // One block step covers one tile (64 chunks) x WAVES consecutive runs: each wavefront one run, each
@@ -897,6 +899,28 @@ void k_ps_sum_tiled(const uint8_t *__restrict__ symt, int64_t n, int U, int64_t 
         const int64_t tile = q >> __builtin_ctz((unsigned)runs_per_chunk);
         const int64_t i0 = (tile * CO3_WAVE + lane) * chunk_syms + (int64_t)run * EPT;
         const uint8_t *src = symt + r * 16;
+        // Users are taken PT_AHEAD at a time, their symbols requested together, the first ones before anything is looked
+        // up: a step that waited for one user's after the other took 0.7 us a user where few steps fill the chip.  (A
+        // single user: the registers for more cost 20 % where its steps fill the chip.)
+        uint4 ahead[PT_AHEAD];
+        auto request = [&](int u0) {
+#pragma unroll
+            for (int q = 0; q < PT_AHEAD; ++q)
+                if (u0 + q < U) ahead[q] = ld_stream_u4(src + (int64_t)(u0 + q) * ws_stride);
+        };
+        if (i0 < n) request(0);
+        // add(u, w): a user's 16 bytes
+        auto each_user = [&](auto add) {
+            for (int u0 = 0; u0 < U; u0 += PT_AHEAD) {
+                if (u0) request(u0);
+#pragma unroll
+                for (int q = 0; q < PT_AHEAD; ++q) {
+                    if (u0 + q >= U) break;
+                    const uint32_t w[4] = {ahead[q].x, ahead[q].y, ahead[q].z, ahead[q].w};
+                    add(u0 + q, w);
+                }
+            }
+        };
         // the sum starts at zero, or continues a sum over users before these (acc_in may be avg_out: every
         // element is read and written by the same workgroup, the reads first)
         float acc[EPT];
@@ -923,11 +947,8 @@ void k_ps_sum_tiled(const uint8_t *__restrict__ symt, int64_t n, int U, int64_t 
             const int bs = co3_find_seg(seg_off, nseg, b0 < n ? b0 : n - 1);
             from_table = bs == co3_find_seg(seg_off, nseg, b1 < n ? b1 : n - 1);     // the same for all threads
             if (from_table && bs != table_seg) {       // (every read of the last values lies before a barrier below)
-                const int H = fc.K >> 1;
-                for (int j = threadIdx.x; j < U * H; j += PT_BLOCK) {
-                    const int u = j / H;
-                    value_of[j] = value((uint32_t)(j - u * H), u, bs);
-                }
+                const int sh = EM + (HALF ? 0 : 1);            // (K is a power of two)
+                for (int j = threadIdx.x; j < U << sh; j += PT_BLOCK) value_of[j] = value((uint32_t)j & ((1u << sh) - 1u), j >> sh, bs);
                 table_seg = bs;
                 __syncthreads();
             }
@@ -939,32 +960,38 @@ void k_ps_sum_tiled(const uint8_t *__restrict__ symt, int64_t n, int U, int64_t 
         }
         if (i0 >= n) {
         } else if (from_table) {
-            for (int u = 0; u < U; ++u) {
-                const float *vu = value_of + u * (TABLE == 1 ? fc.K : fc.K >> 1);
-                uint4 v = ld_stream_u4(src + (int64_t)u * ws_stride);
-                uint32_t w[4] = {v.x, v.y, v.z, v.w};
+            each_user([&](int u, const uint32_t (&w)[4]) {
+                const float *vu = value_of + u * (HALF ? fc.K >> 1 : fc.K);
 #pragma unroll
                 for (int k = 0; k < EPT; ++k) {
                     const uint32_t sy = symbol(w, k);
-                    if (TABLE == 1) acc[k] += vu[sy & ((uint32_t)fc.K - 1u)];
-                    else if (TABLE == 2) acc[k] += __uint_as_float(__float_as_uint(vu[sy & cmask]) | (((sy >> EM) & 1u) << 31));
+                    if (!HALF) acc[k] += vu[sy & ((uint32_t)fc.K - 1u)];
                     else acc[k] += __uint_as_float(__float_as_uint(vu[sy & cmask]) ^ (((sy >> EM) & 1u) << 31));
                 }
-            }
+            });
         } else if (s_lo == s_hi) {
-            for (int u = 0; u < U; ++u) {
+            each_user([&](int u, const uint32_t (&w)[4]) {
                 const int e_min = anchor[(int64_t)u * nseg + s_lo] - F + 1;
                 const float c = scale ? scale[(int64_t)u * nseg + s_lo] : 1.0f;
-                uint4 v = *reinterpret_cast<const uint4 *>(src + (int64_t)u * ws_stride);
-                uint32_t w[4] = {v.x, v.y, v.z, v.w};
+                if (!scale && __all((uint32_t)(e_min + 125) <= (uint32_t)(253 - F))) {
+                    // Anchors as the conversion makes them: the code in the exponent and mantissa of a float that is
+                    // subnormal where the field is 0, times a power of two -- exact.  (21 -> 16 us for one user's 62
+                    // tensors of 11.2 M elements.)
 #pragma unroll
-                for (int k = 0; k < EPT; ++k) {
-                    uint32_t s = symbol(w, k);
-                    float val = co3_code_value(s & cmask, e_min, M);
-                    val = __uint_as_float(__float_as_uint(val) | ((s >> EM) << 31));
-                    acc[k] += scale ? val / c : val;
+                    for (int k = 0; k < EPT; ++k) {
+                        const uint32_t s = symbol(w, k);
+                        acc[k] += ldexpf(__uint_as_float(((s & cmask) << (23 - M)) | ((s >> EM) << 31)), e_min + 126);
+                    }
+                } else {
+#pragma unroll
+                    for (int k = 0; k < EPT; ++k) {
+                        uint32_t s = symbol(w, k);
+                        float val = co3_code_value(s & cmask, e_min, M);
+                        val = __uint_as_float(__float_as_uint(val) | ((s >> EM) << 31));
+                        acc[k] += scale ? val / c : val;
+                    }
                 }
-            }
+            });
         } else {                           // the run straddles tensors: anchor per element
             uint32_t seg_of[EPT];          // looked up once, not for every user
             uint32_t sg = (uint32_t)s_lo;
@@ -977,7 +1004,7 @@ void k_ps_sum_tiled(const uint8_t *__restrict__ symt, int64_t n, int U, int64_t 
                 }
                 seg_of[k] = sg;
             }
-            for (int u = 0; u < U; ++u) {
+            for (int u = 0; u < U; ++u) {      // (few runs: their registers are not worth more requests at a time)
                 const int32_t *anchor_u = anchor + (int64_t)u * nseg;
                 const float *scale_u = scale ? scale + (int64_t)u * nseg : nullptr;
                 uint4 v = *reinterpret_cast<const uint4 *>(src + (int64_t)u * ws_stride);
@@ -992,8 +1019,18 @@ void k_ps_sum_tiled(const uint8_t *__restrict__ symt, int64_t n, int U, int64_t 
                 }
             }
         }
+        if (divisor > 0.f) {
+            // one division, rounded once: by a power of two (a single user among them) it is a multiplication
+            if (pow2) {
 #pragma unroll
-        for (int k = 0; k < EPT; ++k) out_s[lane][wr * EPT + k] = divisor > 0.f ? acc[k] / divisor : acc[k];
+                for (int k = 0; k < EPT; ++k) acc[k] *= recip;
+            } else {
+#pragma unroll
+                for (int k = 0; k < EPT; ++k) acc[k] = acc[k] / divisor;
+            }
+        }
+#pragma unroll
+        for (int k = 0; k < EPT; ++k) out_s[lane][wr * EPT + k] = acc[k];
         __syncthreads();
         const int64_t run0 = (int64_t)(run - wr) * EPT;      // first element (within a chunk) of the block's runs
 #pragma unroll 4
@@ -1088,17 +1125,27 @@ hipError_t co3_launch_ps_sum_tiled(const uint8_t *symt, int64_t n, int U, int64_
     // two users 24.1 | 24.5, three 27.9 | 30.6, sixteen 76 | 113; 11 M in 275 tensors, two 27.2 | 25.0, three 32.3 |
     // 31.6, four 36.7 | 37.8, sixteen 95 | 113).
     const bool tables_pay = nseg > 1 && U >= 3;
-#define CO3_SUM_LAUNCH(T, P, BYTES)                                                                                \
-    hipLaunchKernelGGL((k_ps_sum_tiled<T, P>), dim3(blocks), dim3(threads), BYTES, st, symt, n, U, ws_stride,     \
+#define CO3_SUM_LAUNCH(T, P, A, BYTES)                                                                             \
+    hipLaunchKernelGGL((k_ps_sum_tiled<T, P, A>), dim3(blocks), dim3(threads), BYTES, st, symt, n, U, ws_stride,  \
                        chunk_syms, nruns, anchor, scale, seg_off, nseg, fmt, acc_in, divisor, avg_out)
+    const size_t half_bytes = full_bytes / 2;
+    const int known = co3_device_cus(), cus = known > 0 ? known : 256;
+    // A table of few values, one user at a time where the steps fill the chip anyway (16 x 25 M E3M1, one | four users
+    // at a time: 85.5 | 89 us); two at a time where the registers of more would cost wavefronts.
+    const bool full_chip = blocks >= 16u * (unsigned)cus;
     if (packed) {       // alphabets of at most 16 symbols: the full table is 64 bytes per user
-        if (nseg == 1 && full_bytes <= 4096) CO3_SUM_LAUNCH(1, true, full_bytes);
-        else if (tables_pay && full_bytes / 2 <= 32768) CO3_SUM_LAUNCH(3, true, full_bytes / 2);
-        else CO3_SUM_LAUNCH(0, true, 0);
-    } else if (nseg == 1 && full_bytes <= 4096) CO3_SUM_LAUNCH(1, false, full_bytes);
-    else if (nseg == 1 && full_bytes / 2 <= 32768) CO3_SUM_LAUNCH(2, false, full_bytes / 2);
-    else if (tables_pay && full_bytes / 2 <= 32768) CO3_SUM_LAUNCH(3, false, full_bytes / 2);
-    else CO3_SUM_LAUNCH(0, false, 0);
+        if (nseg == 1 && U == 1) CO3_SUM_LAUNCH(1, true, 1, full_bytes);
+        else if (nseg == 1 && full_bytes <= 4096) CO3_SUM_LAUNCH(1, true, 2, full_bytes);
+        else if (tables_pay && half_bytes <= 32768) CO3_SUM_LAUNCH(3, true, 2, half_bytes);
+        else if (U == 1) CO3_SUM_LAUNCH(0, true, 1, 0);
+        else CO3_SUM_LAUNCH(0, true, 2, 0);
+    } else if (nseg == 1 && U == 1) CO3_SUM_LAUNCH(1, false, 1, full_bytes);
+    else if (nseg == 1 && full_bytes <= 4096 && full_chip) CO3_SUM_LAUNCH(1, false, 1, full_bytes);
+    else if (nseg == 1 && full_bytes <= 4096) CO3_SUM_LAUNCH(1, false, 4, full_bytes);
+    else if (nseg == 1 && half_bytes <= 32768) CO3_SUM_LAUNCH(2, false, 4, half_bytes);
+    else if (tables_pay && half_bytes <= 32768) CO3_SUM_LAUNCH(3, false, 2, half_bytes);
+    else if (U == 1) CO3_SUM_LAUNCH(0, false, 1, 0);
+    else CO3_SUM_LAUNCH(0, false, 2, 0);
 #undef CO3_SUM_LAUNCH
     return hipGetLastError();
 }

@@ -161,6 +161,27 @@ def test_stored_table_of_a_shorter_prefix(co3, bits, longest):
     assert np.array_equal(pipe.sym_dec[0, :n].cpu().numpy(), s)
 
 
+# users are taken four (or two) at a time; a division by a power of two is a multiplication: results down to the
+# smallest subnormal numbers, which both round once
+@pytest.mark.parametrize("E,M", [(3, 0), (3, 1), (4, 3)])
+@pytest.mark.parametrize("U", [1, 2, 4, 5, 8, 9, 63])
+@pytest.mark.parametrize("alpha", [1e-3, 1e-36, 1e-38, 1e-41])
+def test_average_of_users_taken_together(co3, E, M, U, alpha):
+    n = 2_501
+    fmt, f = co3.Fmt(E, M), oracle.Fmt(E, M)
+    r = np.random.default_rng(U * 11 + E)
+    g = (r.standard_normal((U, n)) * alpha).astype(np.float32)
+    pipe = co3.Co3Pipeline(U, n, fmt, chunk_syms=64)
+    buf = pipe.new_gradient_buffer()
+    buf[:, :n] = torch.from_numpy(g).cuda()
+    pipe.step(buf)
+    assert pipe.poll() == 0
+    A = np.array([[oracle.anchor(g[u], f)] for u in range(U)], np.int32).reshape(U, 1)
+    sym = np.stack([oracle.convert_ef(g[u], np.zeros(n, np.float32), int(A[u, 0]), 1.0, f)[0] for u in range(U)])
+    want = oracle.aggregate(sym, A, f)
+    assert np.array_equal(pipe.avg[:n].cpu().numpy().view(np.uint32), want.view(np.uint32))
+
+
 LAYOUTS = {
     "one tile and less": [5000, 3, 0, 900],
     "steps inside tensors": [100_000, 60_001, 7],
