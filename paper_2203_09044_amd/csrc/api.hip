@@ -373,7 +373,7 @@ int32_t co3_user_encode(const float *g, float *err, int64_t n, int32_t U, int64_
                               : co3_launch_build_code(counts, U, fc.K, codes, status, st);
     if (e != hipSuccess) return CO3_EHIP;
     return hip_rc(co3_launch_encode(symbuf, n, U, stride, codes, fc.K, nullptr, 1, words, cap_words, chunk_syms, chunk_bitoff,
-                                    total_bits, static_cast<uint64_t *>(enc_ws), status, st, nib));
+                                    total_bits, static_cast<uint64_t *>(enc_ws), status, st, nib, coop ? 1 : 0));
 }
 
 int32_t co3_moments(const float *g, const float *err, int64_t n, int32_t U, int64_t stride, const int64_t *seg_off,

@@ -83,9 +83,10 @@ __global__ __launch_bounds__(EN_BLOCK) void k_enc_sizes(const uint8_t *__restric
                                                          const void *__restrict__ codes, int K,
                                                          uint64_t *__restrict__ tilesum, int64_t nblk,
                                                          uint64_t *__restrict__ groupsum, int64_t ngrp,
-                                                         int32_t *status, int sym_nib)
+                                                         int32_t *status, int sym_nib, int newest_last)
 {
-    const int u = blockIdx.y;
+    // (the order of the users: see co3_launch_encode)
+    const int u = newest_last ? (int)(gridDim.y - 1 - blockIdx.y) : (int)blockIdx.y;
     const Co3Code *cd = code_of(codes, u);
     __shared__ uint8_t len_s[256];
     __shared__ uint8_t pairlen_s[256];     // symbols two per byte: both lengths together, bit 7 set when one of them is 0
@@ -989,11 +990,14 @@ static int pack_blocks_per_workgroup(int64_t nblk, int U)
     return all >= 16384 ? 4 : all >= 4096 ? 2 : 1;
 }
 
-// seg_off != NULL selects one code per tensor (codes[tensor], shared by the users) instead of codes[user]
+// seg_off != NULL selects one code per tensor (codes[tensor], shared by the users) instead of codes[user].
+// newest_last: the symbols were written user by user, the last user's last.  The sizes pass then takes the users from
+// the last to the first, and the packer from the first on: each begins with what the pass before it has left in the
+// last-level cache (16 x 25 M E4M3, 400 MB of symbols against 256 MB of cache: sizes 120 -> 84 us, packer 162 -> 165).
 hipError_t co3_launch_encode(const uint8_t *sym, int64_t n, int U, int64_t stride, const void *codes, int K,
                              const int64_t *seg_off, int nseg, uint64_t *words, int64_t cap_words, int chunk_syms,
                              uint64_t *chunk_bitoff, uint64_t *total_bits, uint64_t *tilesum, int32_t *status,
-                             hipStream_t st, int sym_nib)
+                             hipStream_t st, int sym_nib, int newest_last)
 {
     if (sym_nib && (seg_off || K > 16)) return hipErrorInvalidValue;
     static_assert(SZ_GROUP == CO3_PACK_GROUP, "group size of the sizes pass");
@@ -1008,7 +1012,7 @@ hipError_t co3_launch_encode(const uint8_t *sym, int64_t n, int U, int64_t strid
                                K, seg_off, nseg, tilesum, nblk, groupsum, ngrp, status);
         else
             hipLaunchKernelGGL(k_enc_sizes, dim3((unsigned)ngrp, U), dim3(EN_BLOCK), 0, st, sym, n, stride, codes, K,
-                               tilesum, nblk, groupsum, ngrp, status, sym_nib);
+                               tilesum, nblk, groupsum, ngrp, status, sym_nib, newest_last);
     }
     static_assert((int64_t)CO3_WAVE * CO3_PACK_GROUP * CO3_PACK_SYMS * 64 < (1ll << 32), "64 groups fit 32 bits");
     const bool scan_in_pack = !seg_off && nblk > 0 && ngrp <= CO3_WAVE;

@@ -55,7 +55,7 @@ int64_t co3_coop_full_elements(int64_t n, int kpt);
 hipError_t co3_launch_encode(const uint8_t *sym, int64_t n, int U, int64_t stride, const void *codes, int K,
                              const int64_t *seg_off, int nseg, uint64_t *words, int64_t cap_words, int chunk_syms,
                              uint64_t *chunk_bitoff, uint64_t *total_bits, uint64_t *tilesum, int32_t *status,
-                             hipStream_t st, int sym_nib = 0);
+                             hipStream_t st, int sym_nib = 0, int newest_last = 0);
 // device address, on the current device, of the library's own fixed encoder workspace of
 // CO3_ENCODE_STATIC_WS_BYTES bytes (looked up on the first call per device; allocates nothing)
 hipError_t co3_static_encode_workspace(void **ptr_out);
