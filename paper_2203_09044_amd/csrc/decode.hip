@@ -30,8 +30,8 @@ __device__ __forceinline__ const Co3Code *dcode_of(const void *codes, int u)
 #define DE_GROUP 16          // symbols per run: one ring refill point, one 16-byte store
 #define DE_MISS_LEN 255u     // length field of a table entry that does not resolve a symbol
 #define DE_PAIR_BITS 12      // prefix length of the two-symbol table used for alphabets of at most 16 symbols
-// Table lookups between two reads of the ring: 4 x 14 bits lie in a window of 64.  That holds for hits alone: a
-// codeword that the table does not resolve (up to CO3_MAX_CODE_LEN bits) is searched in a window read at its start.
+// Table lookups between two reads of the ring: 4 x 14 bits lie in a window of 64.  That holds for hits alone: after a
+// codeword that the table does not resolve (up to CO3_MAX_CODE_LEN bits) the window is read anew where it may fall short.
 #define DE_REFILL 4
 enum { DE_SHORT = 0, DE_LONG = 1, DE_PAIRS = 2, DE_RETRY = 3 };   // fast-path variants of decode_range
 
