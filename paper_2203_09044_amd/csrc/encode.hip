@@ -12,10 +12,13 @@
 #define EN_BLOCK 256
 #define EN_WAVES (EN_BLOCK / CO3_WAVE)
 #define EN_LSYM 16                             // symbols per lane
-#define EN_STAGE_WORDS 128                     // staging window: 8192 bits = 8 bits/symbol on average
+#define EN_STAGE_WORDS 128                     // staging window of a tile: 8192 bits = 8 bits/symbol on average
+#define EN_LONG_STAGE_WORDS 448                // where the LDS is there anyway: 28 bits/symbol
 static_assert(CO3_WAVE * EN_LSYM == CO3_PACK_SYMS, "tile geometry");
 #define EN_WG_SYMS (EN_WAVES * CO3_PACK_SYMS)  // symbols of a workgroup's tiles
 #define EN_WG_WORDS 640                        // staging window of a workgroup: 10 bits/symbol on average
+#define EN_MOST_BLOCKS (CO3_PACK_GROUP / EN_WAVES) // blocks of a group
+#define EN_ALL_WORDS 2016                      // its two windows, and the room of a block of up to 31 bits/symbol
 
 __device__ __forceinline__ const Co3Code *code_of(const void *codes, int u)
 {
@@ -398,14 +401,15 @@ __device__ __forceinline__ void lookup_runs_pairs(const uint64_t *penc_s, uint2 
 
 // ORs `nb` bits (right-aligned in `acc`, 1 <= nb <= 64) into the staging window at stream position
 // `pos` (bits, relative to the first word of the tile); only words inside the window are touched.
+template <int STAGE>
 __device__ __forceinline__ void stage_bits(unsigned long long *stage, int64_t win_w0, uint64_t acc, int nb,
                                            uint64_t pos)
 {
     uint64_t v = acc << (64 - nb);
     int64_t w = (int64_t)(pos >> 6) - win_w0;
     int o = (int)(pos & 63);
-    if (w >= 0 && w < EN_STAGE_WORDS) atomicOr(&stage[w], (unsigned long long)(v >> o));
-    if (o + nb > 64 && w + 1 >= 0 && w + 1 < EN_STAGE_WORDS) atomicOr(&stage[w + 1], (unsigned long long)(v << (64 - o)));
+    if (w >= 0 && w < STAGE) atomicOr(&stage[w], (unsigned long long)(v >> o));
+    if (o + nb > 64 && w + 1 >= 0 && w + 1 < STAGE) atomicOr(&stage[w + 1], (unsigned long long)(v << (64 - o)));
 }
 
 // ---- whole blocks of four tiles packed by a workgroup together ---------------------------------
@@ -415,8 +419,11 @@ __device__ __forceinline__ void stage_bits(unsigned long long *stage, int64_t wi
 // is handed to the window of the next.  What is the same for a wavefront is kept in scalar registers, and codewords are
 // joined in table entries of 32 bits (16 symbols of a lane: 267 -> 175 vector instructions in an 8-bit format, 237 -> 117
 // with two symbols per byte).  Fewer instructions alone gave nothing: a workgroup per block with the same packing took
-// 198 and 49 us below.  10 x 11.2 M E3M0 52 -> 37 us, E4M3 57 -> 45; 16 x 25 M E4M3 199 -> 158 (737 MB at 4.7 TB/s, the
-// rate of a copy); 4 x 11.2 M E4M3 under shared codes 50 -> 35.
+// 198 and 49 us below.  10 x 11.2 M E3M0 52 -> 35.5 us, E4M3 57 -> 46; 16 x 25 M E4M3 199 -> 158 (737 MB at 4.7 TB/s, the
+// rate of a copy); 4 x 11.2 M E4M3 under shared codes 50 -> 31.
+//
+// A block of more than 10 bits a symbol takes the windows' LDS alone (encoding 10 x 11.2 M in E4M3, a fifth | all of the
+// blocks at 23 bits a symbol 136 -> 88 | 328 -> 155 us; with such blocks tile by tile one after the other 163 | 377).
 //
 // An entry is codeword << 8 | length; a codeword of 24 bits or more has only its length there and the top bit set.  A
 // lane with such a codeword, or with two neighbours of 32 bits together, packs its symbols one by one.
@@ -425,7 +432,7 @@ __device__ __forceinline__ void stage_bits(unsigned long long *stage, int64_t wi
 struct PackLds {
     uint64_t enc[256];                         // as in the code
     uint32_t tab[256];                         // per symbol; symbols two per byte: per pair of symbols
-    unsigned long long win[2][EN_WG_WORDS + 2]; // word r of a block's window at EN_WG_WORDS - 1 - r
+    unsigned long long win[EN_ALL_WORDS];      // word r of a window that begins at word b at b + EN_WG_WORDS - 1 - r
 };
 
 __device__ __forceinline__ uint32_t pack_entry(uint64_t code, uint32_t l)
@@ -433,30 +440,34 @@ __device__ __forceinline__ uint32_t pack_entry(uint64_t code, uint32_t l)
     return l >= 24u ? EN_FAR_ENTRY | l : ((uint32_t)code << 8) | l;
 }
 
-#define EN_WIN_BITS ((EN_WG_WORDS + 2) * 64u)   // distance of the two windows
+// Two windows, of blocks in turn; one that takes the whole array, for a block that does not fit these.
+#define EN_WIN_BITS ((EN_WG_WORDS + 2) * 64u)                       // distance of the two windows
+#define EN_WIDE_BITS ((EN_ALL_WORDS - 2 - EN_WG_WORDS) * 64u)       // where the one window begins
 
 // ORs the `nb` <= 64 bits of v (right-aligned) into the windows.  d: distance of their start from the end of the first
-// window (for the second one EN_WIN_BITS more), on return that of their end; what of v lies before the word that holds
+// window (for the others their beginning more), on return that of their end; what of v lies before the word that holds
 // their end goes to the word before, which is the next one in the array.
 __device__ __forceinline__ void pack_put(PackLds &L, uint64_t v, uint32_t nb, uint32_t &d)
 {
     d -= nb;
-    unsigned long long *w = L.win[0] + (d >> 6);
+    unsigned long long *w = L.win + (d >> 6);
     atomicOr(w, (unsigned long long)(v << (d & 63u)));
     if ((d & 63u) + nb > 64u) atomicOr(w + 1, (unsigned long long)(v >> ((0u - d) & 63u)));
 }
 
-// `blocks` blocks from element i0 on, all of one code.  where(group_base, end_bit): stream positions of their group of
-// tiles and of their end (called behind the first barrier, when what it is made from has arrived with the symbols and
-// the table); toff: positions of their tiles in the group.  Returns false (to all threads) where a block does not fit
-// its window or the stream its capacity; nothing has been written then.
-template <bool NIB, class Where>
-__device__ __forceinline__ bool pack_blocks(PackLds &L, const uint8_t *su, const Co3Code *cd, int K, int64_t n, int64_t i0,
-                                            int blocks, int wave, int lane, Where where, const uint64_t *__restrict__ toff,
-                                            uint64_t *__restrict__ wu, int64_t cap_words, int chunk_syms,
+// Up to `blocks` blocks from element i0 on, all of one code.  where(request(lane), tid, group_base, group_end): stream positions of their
+// group of tiles and of its end (called behind the first barrier, when what it is made from has arrived with the symbols
+// and the table); toff: positions of their tiles in the group, up to tile `tiles_end` (from the first block's on), where
+// the group ends.  Takes the blocks up to the first one that does not fit a window or ends behind the stream's capacity;
+// a first one that fits the whole array alone.  Returns their number (to all threads).
+template <bool NIB, class Request, class Where>
+__device__ __forceinline__ int pack_blocks(PackLds &L, const uint8_t *su, const Co3Code *cd, int K, int64_t n, int64_t i0,
+                                            int blocks, int wave, int tid, Request request, Where where, const uint64_t *__restrict__ toff,
+                                            int tiles_end, uint64_t *__restrict__ wu, int64_t cap_words, int chunk_syms,
                                             uint64_t *__restrict__ chunk_off)
 {
     constexpr int G = EN_LSYM / 4;
+    const int lane = tid & (CO3_WAVE - 1);
     const int64_t iw = i0 + (int64_t)wave * CO3_PACK_SYMS;
     const uint8_t *src = su + (NIB ? iw >> 1 : iw);                      // uniform
     const uint32_t lane_at = (uint32_t)lane * (NIB ? EN_LSYM / 2 : EN_LSYM);
@@ -468,12 +479,15 @@ __device__ __forceinline__ bool pack_blocks(PackLds &L, const uint8_t *su, const
         return *reinterpret_cast<const uint4 *>(src + lane_at);
     };
     uint4 nxt = load();
+    const uint64_t requested = request(lane);
+    // offsets of the tiles in the group, one a lane (they fit 32 bits)
+    const uint32_t tile_offs = lane < tiles_end ? (uint32_t)toff[lane] : 0u;
     // the symbols that follow the last block: their codewords complete its last word
-    const int64_t i_end = i0 + (int64_t)blocks * EN_WG_SYMS;
-    const bool ahead = wave == EN_WAVES - 1 && lane < CO3_WAVE - 1 && i_end + lane < n;
-    const uint32_t next_sym = ahead ? load_sym1(su, i_end + lane, NIB) : 0u;
+    int64_t i_end = i0 + (int64_t)blocks * EN_WG_SYMS;
+    bool ahead = wave == EN_WAVES - 1 && lane < CO3_WAVE - 1 && i_end + lane < n;
+    uint32_t next_sym = ahead ? load_sym1(su, i_end + lane, NIB) : 0u;
     {
-        const int j = threadIdx.x;
+        const int j = tid;
         static_assert(EN_BLOCK == 256, "a table entry per thread");
         const uint64_t e = j < K ? cd->enc[j] : 0ull;
         L.enc[j] = e;
@@ -487,21 +501,37 @@ __device__ __forceinline__ bool pack_blocks(PackLds &L, const uint8_t *su, const
         }
         for (int q = j; q < EN_WG_WORDS + 2; q += EN_BLOCK) reinterpret_cast<ulonglong2 *>(L.win)[q] = make_ulonglong2(0ull, 0ull);
     }
-    const uint64_t off0 = toff[0];
     __syncthreads();
-    uint64_t group_base, end_bit;
-    where(group_base, end_bit);
+    uint64_t group_base, group_end;
+    where(requested, tid, group_base, group_end);
+    const uint32_t last_off = (uint32_t)(group_end - group_base);
+    const uint32_t offs = lane < tiles_end ? tile_offs : last_off;
+    auto tile_off = [&](int t) -> uint32_t { return (uint32_t)__builtin_amdgcn_readlane((int)offs, t); };
+    const uint32_t off0 = tile_off(0);
+    bool wide = false;                         // one block, alone in the whole array
     {
-        bool fits = (int64_t)((end_bit + 63) >> 6) <= cap_words;
-        uint64_t from = off0;
-        for (int k = 1; k <= blocks; ++k) {
-            const uint64_t to = k < blocks ? toff[k * EN_WAVES] : end_bit - group_base;
-            fits = fits && to - from <= EN_WG_WORDS * 64u - 63u;
-            from = to;
+        const uint64_t cap_bits = (uint64_t)cap_words * 64u;
+        const uint64_t left = cap_bits > group_base ? cap_bits - group_base : 0ull;
+        const uint32_t most = left < 0xffffffffull ? (uint32_t)left : 0xffffffffu;
+        // lane 4 k: the end of block k, from the lane four on (a group has 16 tiles, a row of lanes: its last block ends with it)
+        static_assert(CO3_PACK_GROUP == 16 && EN_WAVES == 4, "a block's end lies four lanes on in a row of 16");
+        const uint32_t to = (uint32_t)__builtin_amdgcn_update_dpp((int)last_off, (int)offs, 0x104, 0xf, 0xf, false);   // row_shl:4
+        const uint32_t size = to - offs;
+        const uint32_t fits = (uint32_t)__ballot(to <= most && size <= EN_WG_WORDS * 64u - 63u);
+        const int fit = __builtin_ctz((~fits & 0x1111u) | 0x10000u) / EN_WAVES;
+        if (fit < blocks) {
+            if (fit == 0) {
+                if ((__ballot(to <= most && size <= (EN_ALL_WORDS - 2) * 64u - 63u) & 1u) == 0u) return 0;
+                wide = true;
+            }
+            blocks = wide ? 1 : fit;
+            i_end = i0 + (int64_t)blocks * EN_WG_SYMS;
+            ahead = wave == EN_WAVES - 1 && lane < CO3_WAVE - 1 && i_end + lane < n;
+            next_sym = ahead ? load_sym1(su, i_end + lane, NIB) : 0u;
         }
-        if (!fits) {
-            __syncthreads();                   // the general path uses the same LDS
-            return false;
+        if (wide) {
+            for (int q = tid + 2 * (EN_WG_WORDS + 2); q < EN_ALL_WORDS; q += EN_BLOCK) L.win[q] = 0ull;
+            __syncthreads();
         }
     }
 
@@ -511,18 +541,16 @@ __device__ __forceinline__ bool pack_blocks(PackLds &L, const uint8_t *su, const
     const uint32_t chunk_sh = (uint32_t)__builtin_ctz((unsigned)chunk_syms);
     const uint32_t chunk_at = (uint32_t)(lane * EN_LSYM) >> chunk_sh;
     int64_t tile_i = iw;
-    const uint64_t *tp = toff;
 #pragma unroll 1
     for (int k = 0; k < blocks; ++k) {
         const bool last = k + 1 == blocks;
         const uint32_t s[4] = {nxt.x, nxt.y, nxt.z, nxt.w};
         src += NIB ? EN_WG_SYMS / 2 : EN_WG_SYMS;
         if (!last) nxt = load();
-        const uint32_t tile_rel = (uint32_t)tp[wave] - (uint32_t)tp[0];
-        const uint64_t base_next = last ? end_bit : group_base + tp[EN_WAVES];
-        tp += EN_WAVES;
+        const uint32_t tile_rel = tile_off(k * EN_WAVES + wave) - tile_off(k * EN_WAVES);
+        const uint64_t base_next = group_base + tile_off((k + 1) * EN_WAVES);
         const uint32_t base_bit = (uint32_t)base & 63u;
-        const uint32_t win = k & 1 ? EN_WIN_BITS : 0u;
+        const uint32_t win = wide ? EN_WIDE_BITS : k & 1 ? EN_WIN_BITS : 0u;
 
         // codewords of four symbols joined, right-aligned
         uint64_t run[G];
@@ -581,26 +609,26 @@ __device__ __forceinline__ bool pack_blocks(PackLds &L, const uint8_t *su, const
             const uint32_t o = wave_scan_incl_u32(l, lane) - l + (end & 63u);
             uint32_t at = (win >> 6) + EN_WG_WORDS - 1 - (end >> 6);
             asm volatile("" : "+v"(at));       // one word for all lanes: the compiler would gather them one by one
-            if (l && o < 64u) atomicOr(L.win[0] + at, (unsigned long long)(((e >> 6) << (64u - l)) >> o));
+            if (l && o < 64u) atomicOr(L.win + at, (unsigned long long)(((e >> 6) << (64u - l)) >> o));
         }
         __syncthreads();
         // Words leave in order; what has been read is cleared for the block after the next.
         const uint32_t whole = end >> 6, nw = (end + 63u) >> 6;
         uint64_t *dst = wu + (base >> 6);
-        for (uint32_t r = threadIdx.x; r < nw; r += EN_BLOCK) {
-            unsigned long long *w = L.win[0] + ((win >> 6) + EN_WG_WORDS - 1 - r);
+        for (uint32_t r = (uint32_t)tid; r < nw; r += EN_BLOCK) {
+            unsigned long long *w = L.win + ((win >> 6) + EN_WG_WORDS - 1 - r);
             const unsigned long long v = *w;
             *w = 0ull;
             if (r >= whole && !last) {         // (one thread) the unfinished word: the next window's first
                 uint32_t at = ((EN_WIN_BITS - win) >> 6) + EN_WG_WORDS - 1;
                 asm volatile("" : "+v"(at));
-                atomicOr(L.win[0] + at, v);
+                atomicOr(L.win + at, v);
             } else if (r != 0u || !foreign) dst[r] = v;
         }
         foreign = foreign && whole == 0u;
         base = base_next;
     }
-    return true;
+    return blocks;
 }
 
 // The general path: a wavefront packs its own tile tb, of any size and with any codes, through a window of its own.
@@ -623,9 +651,11 @@ __device__ __forceinline__ void load_tile(const uint8_t *su, bool nib, int64_t n
 }
 
 // LAYERS: a tile that straddles tensors (look-ahead included) reads its entries from the code blobs, tensor by element.
-template <bool LAYERS>
-__device__ __forceinline__ void pack_tile(const uint32_t (&s)[4], uint2 raw, int nvalid, uint32_t next_sym, bool has_next, bool nib, int64_t n, const void *codes, int K, const int64_t *seg_off,
-                                          int nseg, int64_t tb, int lane, uint64_t *enc_s, const uint64_t *penc_s,
+// STAGE: words of the window; a tile of short codewords uses EN_STAGE_WORDS of them.
+template <bool LAYERS, int STAGE>
+__device__ __forceinline__ void pack_tile(const uint32_t (&s)[4], uint2 raw, int nvalid, uint32_t next_sym, bool has_next, bool nib,
+                                          int64_t n, const void *codes, int K, const int64_t *seg_off, int nseg, int64_t tb, int lane,
+                                          uint64_t *enc_s, const uint64_t *penc_s,
                                           unsigned long long *stage, uint32_t maxlen, uint64_t B0, uint64_t *wu, int64_t cap_words,
                                           int chunk_syms, uint64_t *chunk_off)
 {
@@ -748,15 +778,15 @@ __device__ __forceinline__ void pack_tile(const uint32_t (&s)[4], uint2 raw, int
         return;
     }
 
-    for (int64_t win_w0 = 0; gw0 + win_w0 <= gwl; win_w0 += EN_STAGE_WORDS) {
+    for (int64_t win_w0 = 0; gw0 + win_w0 <= gwl; win_w0 += STAGE) {
 #pragma unroll
-        for (int j = 0; j < EN_STAGE_WORDS / CO3_WAVE; ++j) stage[lane + j * CO3_WAVE] = 0ull;
+        for (int j = 0; j < STAGE / CO3_WAVE; ++j) stage[lane + j * CO3_WAVE] = 0ull;
         wave_lds_sync();
         if (!wide) {
             uint64_t pos = rel0;
 #pragma unroll
             for (int g = 0; g < EN_LSYM / 4; ++g) {
-                if (runbits[g]) stage_bits(stage, win_w0, run[g], (int)runbits[g], pos);
+                if (runbits[g]) stage_bits<STAGE>(stage, win_w0, run[g], (int)runbits[g], pos);
                 pos += runbits[g];
             }
         } else {
@@ -768,7 +798,7 @@ __device__ __forceinline__ void pack_tile(const uint32_t (&s)[4], uint2 raw, int
                 int l = (int)(e & 63u);
                 if (l) {
                     if (accbits + l > 64) {
-                        stage_bits(stage, win_w0, acc, accbits, pos);
+                        stage_bits<STAGE>(stage, win_w0, acc, accbits, pos);
                         pos += accbits;
                         acc = 0;
                         accbits = 0;
@@ -777,12 +807,12 @@ __device__ __forceinline__ void pack_tile(const uint32_t (&s)[4], uint2 raw, int
                     accbits += l;
                 }
             }
-            if (accbits) stage_bits(stage, win_w0, acc, accbits, pos);
+            if (accbits) stage_bits<STAGE>(stage, win_w0, acc, accbits, pos);
         }
         // The last word of the tile is completed with the first codewords of the symbols that follow
         // (at most 63 bits, hence at most 63 symbols), clipped at the word end.
         const int64_t last_rel = gwl - gw0 - win_w0;
-        if ((B1 & 63) && last_rel >= 0 && last_rel < EN_STAGE_WORDS) {
+        if ((B1 & 63) && last_rel >= 0 && last_rel < STAGE) {
             uint64_t e = has_next ? entry_at(next_sym, i2) : 0ull;
             uint32_t l = (uint32_t)(e & 63u);
             uint32_t o = wave_scan_incl_u32(l, lane) - l;
@@ -792,7 +822,7 @@ __device__ __forceinline__ void pack_tile(const uint32_t (&s)[4], uint2 raw, int
         }
         wave_lds_sync();
 #pragma unroll
-        for (int j = 0; j < EN_STAGE_WORDS / CO3_WAVE; ++j) {
+        for (int j = 0; j < STAGE / CO3_WAVE; ++j) {
             int64_t gw = gw0 + win_w0 + lane + j * CO3_WAVE;
             if (gw >= first_owned && gw <= gwl) wu[gw] = stage[lane + j * CO3_WAVE];
         }
@@ -832,11 +862,11 @@ __device__ __forceinline__ uint32_t scan_groups(uint32_t bits, int lane, bool re
     return upto;
 }
 
-template <bool LAYERS>
+template <bool LAYERS, int STAGE>
 struct TileLds {
     uint64_t enc_all[LAYERS ? EN_WAVES * 256 : 256];
     uint64_t penc_s[LAYERS ? 1 : 256];           // codeword pairs, symbols two per byte
-    unsigned long long stage_all[EN_WAVES][EN_STAGE_WORDS];
+    unsigned long long stage_all[EN_WAVES][STAGE];
 };
 
 // A tile per wavefront.  LAYERS = false: one code per user (codes[u]), its table shared by the workgroup.  LAYERS = true:
@@ -853,7 +883,7 @@ void k_enc_pack(const uint8_t *__restrict__ sym, int64_t n, int64_t stride, cons
 {
     const int u = blockIdx.y;
     const bool nib = !LAYERS && sym_nib != 0;
-    __shared__ TileLds<LAYERS> lds;
+    __shared__ TileLds<LAYERS, EN_STAGE_WORDS> lds;
     __shared__ int64_t seg_cache[LAYERS ? CO3_SEG_CACHE : 1];
     const int lane = threadIdx.x & (CO3_WAVE - 1);
     const int wave = threadIdx.x / CO3_WAVE;
@@ -884,93 +914,112 @@ void k_enc_pack(const uint8_t *__restrict__ sym, int64_t n, int64_t stride, cons
         const int grp = __builtin_amdgcn_readfirstlane((int)(tb / CO3_PACK_GROUP));
         group_base = grp ? (uint32_t)__builtin_amdgcn_readlane((int)upto, grp - 1) : 0u;
     }
-    pack_tile<LAYERS>(s, raw, nvalid, next_sym, has_next, nib, n, codes, K, seg_off, nseg, tb, lane, lds.enc_all + (LAYERS ? wave * 256 : 0), lds.penc_s,
-                      lds.stage_all[wave], maxlen, group_base + tile_base, words + (int64_t)u * cap_words, cap_words, chunk_syms,
-                      chunk_off);
+    pack_tile<LAYERS, EN_STAGE_WORDS>(s, raw, nvalid, next_sym, has_next, nib, n, codes, K, seg_off, nseg, tb, lane,
+                                      lds.enc_all + (LAYERS ? wave * 256 : 0), lds.penc_s, lds.stage_all[wave], maxlen,
+                                      group_base + tile_base, words + (int64_t)u * cap_words, cap_words, chunk_syms, chunk_off);
 }
 
-// `blocks` blocks of four tiles per workgroup (2 or 4, a group of tiles at most): together where they are whole and of one
-// code, else tile by tile.
-template <bool LAYERS, bool SCAN>
+// A workgroup takes a group of tiles: blocks that are whole and of one code together, up to four in a row, the others
+// (the end of a user's vector, blocks that hold a tensor boundary, that end behind the capacity or that take more than 31
+// bits a symbol) tile by tile.
+template <bool LAYERS, bool SCAN, bool NIB>
 __global__ __launch_bounds__(EN_BLOCK) __attribute__((amdgpu_waves_per_eu(LAYERS ? 5 : 8, LAYERS ? 5 : 8)))
 void k_enc_pack_blocks(const uint8_t *__restrict__ sym, int64_t n, int64_t stride, const void *__restrict__ codes, int K,
                        const int64_t *__restrict__ seg_off_g, int nseg, const uint64_t *__restrict__ tileoff, int64_t nblk,
                        const uint64_t *__restrict__ groupoff, int64_t ngrp, uint64_t *__restrict__ words, int64_t cap_words,
-                       int chunk_syms, uint64_t *__restrict__ chunk_bitoff, int64_t nchunks, int sym_nib,
-                       uint64_t *__restrict__ total_bits, int32_t *status, int blocks)
+                       int chunk_syms, uint64_t *__restrict__ chunk_bitoff, int64_t nchunks, int /*sym_nib*/,
+                       uint64_t *__restrict__ total_bits, int32_t *status)
 {
     const int u = blockIdx.y;
-    const bool nib = !LAYERS && sym_nib != 0;
     __shared__ union {
         PackLds wg;
-        TileLds<LAYERS> tile;
+        TileLds<LAYERS, EN_LONG_STAGE_WORDS> tile;
     } lds;
     __shared__ int64_t seg_cache[LAYERS ? CO3_SEG_CACHE : 1];
-    const int lane = threadIdx.x & (CO3_WAVE - 1);
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / CO3_WAVE);
-    static_assert(CO3_PACK_GROUP % EN_WAVES == 0, "the tiles of a workgroup lie in one group");
-    const int64_t tb0 = (int64_t)blockIdx.x * EN_WAVES * blocks;
-    const int64_t i0 = tb0 * CO3_PACK_SYMS, i_end = i0 + (int64_t)blocks * EN_WG_SYMS;
-    const int64_t grp = tb0 / CO3_PACK_GROUP;
-    const uint8_t *su = sym + (int64_t)u * (nib ? stride / 2 : stride);
+    const int64_t grp = blockIdx.x, tb0 = grp * CO3_PACK_GROUP, i0 = tb0 * CO3_PACK_SYMS;
+    const uint8_t *su = sym + (int64_t)u * (NIB ? stride / 2 : stride);
     uint64_t *wu = words + (int64_t)u * cap_words;
     uint64_t *chunk_off = chunk_bitoff + (int64_t)u * (nchunks + 1);
     const uint64_t *toff = tileoff + (int64_t)u * nblk + tb0;
-    // stream positions of the workgroup's group of tiles and of its end: requested here, made when needed
-    const bool ends_inside = (tb0 + EN_WAVES * blocks) % CO3_PACK_GROUP != 0 && tb0 + EN_WAVES * blocks < nblk;
-    const uint64_t end_off = ends_inside ? toff[EN_WAVES * blocks] : 0ull;
-    uint32_t group_bits = 0;
-    uint64_t group_off = 0, group_next = 0;
-    if (SCAN) group_bits = lane < (int)ngrp ? (uint32_t)groupoff[(int64_t)u * ngrp + lane] : 0u;   // (64 groups fit 32 bits)
-    else {
-        group_off = groupoff[(int64_t)u * ngrp + grp];
-        group_next = grp + 1 < ngrp ? groupoff[(int64_t)u * ngrp + grp + 1] : total_bits[u];
-    }
-    auto where = [&](uint64_t &group_base, uint64_t &end_bit) {
-        group_base = group_off;
-        uint64_t group_end = group_next;
+    // Stream positions of the workgroup's group of tiles and of its end: requested beside the symbols, made when needed.
+    // SCAN: lane g the bits of group g (64 groups fit 32 bits); else an even lane the first position, an odd one the last.
+    auto request = [&](int lane) -> uint64_t {
+        int64_t of_user = (int64_t)u * ngrp;
+        asm volatile("" : "+s"(of_user));          // (not before the loop: it would be waited for before all other requests)
+        const uint64_t *g = groupoff + of_user;
+        if (SCAN) return lane < (int)ngrp ? g[lane] : 0ull;
+        const uint64_t *next = grp + 1 < ngrp ? g + grp + 1 : total_bits + u;
+        return *(lane & 1 ? next : g + grp);
+    };
+    auto where = [&](uint64_t requested, int tid, uint64_t &group_base, uint64_t &group_end) {
+        const uint32_t lo = (uint32_t)requested, hi = (uint32_t)(requested >> 32);
         if (SCAN) {
-            const uint32_t upto = scan_groups(group_bits, lane, tb0 + wave == 0, total_bits + u, chunk_off + nchunks, cap_words, status);
+            const uint32_t upto = scan_groups(lo, tid & (CO3_WAVE - 1), blockIdx.x == 0 && tid < CO3_WAVE, total_bits + u,
+                                              chunk_off + nchunks, cap_words, status);
             group_base = grp ? (uint32_t)__builtin_amdgcn_readlane((int)upto, (int)grp - 1) : 0u;
             group_end = (uint32_t)__builtin_amdgcn_readlane((int)upto, (int)grp);
+        } else {
+            auto of_lane = [&](int l) -> uint64_t {
+                return (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)hi, l) << 32 | (uint32_t)__builtin_amdgcn_readlane((int)lo, l);
+            };
+            group_base = of_lane(0);
+            group_end = of_lane(1);
         }
-        end_bit = ends_inside ? group_base + end_off : group_end;
     };
     const int64_t *seg_off = LAYERS ? co3_cache_segs(seg_off_g, nseg, seg_cache) : seg_off_g;
+    const int tiles_end = nblk - tb0 < CO3_PACK_GROUP ? (int)(nblk - tb0) : CO3_PACK_GROUP;
 
-    if (i_end <= n) {
-        // whole blocks; the codes of their symbols and of the at most 63 behind them that complete the last word
-        int code = u;
-        bool together = true;
-        if (LAYERS) {
-            const int64_t i_last = (i_end + CO3_WAVE - 1 < n ? i_end + CO3_WAVE - 1 : n) - 1;
-            code = __builtin_amdgcn_readfirstlane(co3_find_seg(seg_off, nseg, i0));
-            together = __builtin_amdgcn_readfirstlane(co3_find_seg(seg_off, nseg, i_last)) == code;
-        }
-        if (!together) {
-        } else if (nib) {
-            if (pack_blocks<true>(lds.wg, su, code_of(codes, code), K, n, i0, blocks, wave, lane, where, toff, wu, cap_words,
-                                  chunk_syms, chunk_off)) return;
-        } else if (pack_blocks<false>(lds.wg, su, code_of(codes, code), K, n, i0, blocks, wave, lane, where, toff, wu, cap_words,
-                                      chunk_syms, chunk_off)) return;
-    }
-
-    const uint32_t maxlen = LAYERS ? 0u : load_tile_tables(lds.tile.enc_all, lds.tile.penc_s, code_of(codes, u), K, nib);
-    __syncthreads();
-    uint64_t group_base, end_bit;
-    where(group_base, end_bit);
+    // (looking for blocks of one code costs more than it finds: see pack_by_groups)
+    const bool short_codes = LAYERS && n < nseg * (int64_t)EN_MOST_BLOCKS * EN_WG_SYMS;
+    bool together = false, apart = false;                // how the LDS is used since the last barrier
 #pragma unroll 1
-    for (int k = 0; k < blocks; ++k) {
-        const int64_t tb = tb0 + k * EN_WAVES + wave;
-        if (tb >= nblk) break;
-        uint32_t s[4], next_sym;
-        uint2 raw;
-        int nvalid;
-        bool has_next;
-        load_tile(su, nib, n, tb, lane, s, raw, nvalid, next_sym, has_next);
-        pack_tile<LAYERS>(s, raw, nvalid, next_sym, has_next, nib, n, codes, K, seg_off, nseg, tb, lane,
-                          lds.tile.enc_all + (LAYERS ? wave * 256 : 0), lds.tile.penc_s, lds.tile.stage_all[wave], maxlen,
-                          group_base + toff[k * EN_WAVES + wave], wu, cap_words, chunk_syms, chunk_off);
+    for (int k = 0; k * EN_WAVES < tiles_end;) {
+        int tid = threadIdx.x;                           // what is made from it stays inside the loop: registers
+        asm volatile("" : "+v"(tid));
+        const int lane = tid & (CO3_WAVE - 1), wave = __builtin_amdgcn_readfirstlane(tid / CO3_WAVE);
+        const int64_t ik = i0 + (int64_t)k * EN_WG_SYMS;
+        // blocks to pack together: whole ones, of one code with the at most 63 symbols behind each (its last word)
+        int64_t room = n - ik;
+        int code = u;
+        if (LAYERS && short_codes) room = 0;
+        else if (LAYERS) {
+            code = __builtin_amdgcn_readfirstlane(co3_find_seg(seg_off, nseg, ik));
+            const int64_t end = code + 1 < nseg ? seg_off[code + 1] : n;
+            if (end < n) room = end - (CO3_WAVE - 1) - ik;
+        }
+        const int most = (EN_MOST_BLOCKS - k) * EN_WG_SYMS;
+        int m = __builtin_amdgcn_readfirstlane((room < 0 ? 0 : room < most ? (int)room : most) / EN_WG_SYMS);
+        if (m > 0) {
+            if (together || apart) __syncthreads();
+            together = true;
+            apart = false;
+            m = pack_blocks<NIB>(lds.wg, su, code_of(codes, code), K, n, ik, m, wave, tid, request, where, toff + k * EN_WAVES,
+                                 tiles_end - k * EN_WAVES, wu, cap_words, chunk_syms, chunk_off);
+        }
+        if (m == 0) {                                    // one block tile by tile
+            m = 1;
+            if (together || (!LAYERS && apart)) __syncthreads();
+            together = false;
+            apart = true;
+            const uint32_t maxlen = LAYERS ? 0u : load_tile_tables(lds.tile.enc_all, lds.tile.penc_s, code_of(codes, u), K, NIB);
+            if (!LAYERS) __syncthreads();
+            const uint64_t requested = request(lane);
+            const int64_t tb = tb0 + k * EN_WAVES + wave;
+            const uint64_t tile_base = tb < nblk ? toff[k * EN_WAVES + wave] : 0ull;
+            uint32_t s[4], next_sym;
+            uint2 raw;
+            int nvalid;
+            bool has_next;
+            load_tile(su, NIB, n, tb, lane, s, raw, nvalid, next_sym, has_next);
+            uint64_t group_base, group_end;
+            where(requested, tid, group_base, group_end);
+            if (tb < nblk)
+                pack_tile<LAYERS, EN_LONG_STAGE_WORDS>(s, raw, nvalid, next_sym, has_next, NIB, n, codes, K, seg_off, nseg, tb, lane,
+                                                       lds.tile.enc_all + (LAYERS ? wave * 256 : 0), lds.tile.penc_s,
+                                                       lds.tile.stage_all[wave], maxlen, group_base + tile_base, wu, cap_words,
+                                                       chunk_syms, chunk_off);
+        }
+        k += m;
     }
 }
 
@@ -983,14 +1032,23 @@ hipError_t co3_launch_enc_scan(uint64_t *sizes, int64_t nsizes, int U, int64_t c
     return hipGetLastError();
 }
 
-// Blocks of four tiles that a workgroup of the packer takes in a row; 1: a tile per wavefront.  Few workgroups end sooner
-// with little each: 16 blocks (one user of 65,536 elements) 4.4 | 5.9 | 7.0 us with 1 | 2 | 4, 302 blocks 5.3 | 7.9 | 7.9;
-// 2,728 (one user's ResNet-18) 10.6 | 10.3 | 10.7 and no gain in its pass; 10,916 (four users', shared codes) 50 | 35.0 |
-// 35.9; 27,280 (ten users, E3M0) 52 | 43.8 | 37.
-static int pack_blocks_per_workgroup(int64_t nblk, int U)
+// Whether a workgroup of the packer takes a group of four blocks (else a tile per wavefront).  Few workgroups end sooner
+// with little each (packer of one user, us with a tile per wavefront | four blocks: 8 M E3M0 8.8 | 9.4, E4M3 9.4 | 11.1;
+// 16 M 12.6 | 11.6 and 13.7 | 14.0; 20 M 14.7 | 12.7 and 15.6 | 15.2): from 4,096 blocks on.  And the groups have to hold
+// blocks that can be packed together.  Codes per user: a last group that holds one block, or one or two and a ragged end,
+// takes as long as a whole one or longer, which shows where users have few groups (encoding 100 M symbols in E4M3 by users
+// of one block 83 | 92 us, of two 72 | 64.5, three 70 | 59, four 70 | 58, five 72 | 80, six 70 | 70, nine 69 | 60.5; 200 M
+// by users of 10,000 symbols 173 | 180).
+// Shared codes of groups of tensors that are no longer than the packer's mostly hold a boundary and go tile by tile,
+// which pays for a full chip alone (encoding in E4M3 under codes of 3,000 symbols, 4 x 11 M 363 | 351, 30 M of one user 293
+// | 321, 10 x 11 M 800 | 740; of 5,000 277 | 261, 235 | 240, 610 | 555; of 9,000 226 | 226, 180 | 194, 484 | 473; of 17,000
+// 184 | 165, 154 | 138, 385 | 338; of 40,000 91 | 73, 96 | 77, 197 | 148).
+static bool pack_by_groups(int64_t n, int U, int ncodes)
 {
-    const int64_t all = (nblk + EN_WAVES - 1) / EN_WAVES * U;
-    return all >= 16384 ? 4 : all >= 4096 ? 2 : 1;
+    const int64_t block = EN_WG_SYMS, group = EN_MOST_BLOCKS * block, last = n % group;
+    if ((n + block - 1) / block * U < 4096) return false;
+    if (ncodes) return n / ncodes >= group || (n + block - 1) / block * U >= 16384;
+    return n >= 2 * group || last >= 3 * block || (last % block == 0 && last != block);
 }
 
 // seg_off != NULL selects one code per tensor (codes[tensor], shared by the users) instead of codes[user].
@@ -1022,20 +1080,22 @@ hipError_t co3_launch_encode(const uint8_t *sym, int64_t n, int U, int64_t strid
     if (!scan_in_pack && co3_launch_enc_scan(groupsum, ngrp, U, cap_words, chunk_bitoff, nchunks, total_bits, status, st) != hipSuccess)
         return hipGetLastError();
     if (nblk > 0) {
-        const int blocks = pack_blocks_per_workgroup(nblk, U);
-        const unsigned gx = (unsigned)((nblk + EN_WAVES * blocks - 1) / (EN_WAVES * blocks));
+        const bool groups = pack_by_groups(n, U, seg_off ? nseg : 0);
+        const unsigned gx = (unsigned)(groups ? ngrp : (nblk + EN_WAVES - 1) / EN_WAVES);
         Co3LaunchTimer tm(CO3_K_ENC_PACK, st);
-#define CO3_PACK_LAUNCH(KERNEL, ...)                                                                                   \
-    hipLaunchKernelGGL(KERNEL, dim3(gx, U), dim3(EN_BLOCK), 0, st, sym, n, stride, codes, K, seg_off, nseg,             \
+#define CO3_PACK_LAUNCH(...)                                                                                           \
+    hipLaunchKernelGGL((__VA_ARGS__), dim3(gx, U), dim3(EN_BLOCK), 0, st, sym, n, stride, codes, K, seg_off, nseg,      \
                        (const uint64_t *)tilesum, nblk, (const uint64_t *)groupsum, ngrp, words, cap_words, chunk_syms, \
-                       chunk_bitoff, nchunks, sym_nib, total_bits, status __VA_OPT__(,) __VA_ARGS__)
-        if (blocks > 1) {
-            if (seg_off) CO3_PACK_LAUNCH((k_enc_pack_blocks<true, false>), blocks);
-            else if (scan_in_pack) CO3_PACK_LAUNCH((k_enc_pack_blocks<false, true>), blocks);
-            else CO3_PACK_LAUNCH((k_enc_pack_blocks<false, false>), blocks);
-        } else if (seg_off) CO3_PACK_LAUNCH((k_enc_pack<true, false>));
-        else if (scan_in_pack) CO3_PACK_LAUNCH((k_enc_pack<false, true>));
-        else CO3_PACK_LAUNCH((k_enc_pack<false, false>));
+                       chunk_bitoff, nchunks, sym_nib, total_bits, status)
+        if (groups) {
+            if (seg_off) CO3_PACK_LAUNCH(k_enc_pack_blocks<true, false, false>);
+            else if (scan_in_pack && sym_nib) CO3_PACK_LAUNCH(k_enc_pack_blocks<false, true, true>);
+            else if (scan_in_pack) CO3_PACK_LAUNCH(k_enc_pack_blocks<false, true, false>);
+            else if (sym_nib) CO3_PACK_LAUNCH(k_enc_pack_blocks<false, false, true>);
+            else CO3_PACK_LAUNCH(k_enc_pack_blocks<false, false, false>);
+        } else if (seg_off) CO3_PACK_LAUNCH(k_enc_pack<true, false>);
+        else if (scan_in_pack) CO3_PACK_LAUNCH(k_enc_pack<false, true>);
+        else CO3_PACK_LAUNCH(k_enc_pack<false, false>);
 #undef CO3_PACK_LAUNCH
     }
     return hipGetLastError();

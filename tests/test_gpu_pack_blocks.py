@@ -149,3 +149,89 @@ def test_beyond_the_capacity(co3, short):
     for u, r in ((0, 0), (2, 0), (3, 1), (U - 1, 1)):
         ww, _, t = oracle.encode(rows[r], lengths, codes, C)
         assert np.array_equal(pipe.words[u, :(t + 63) // 64].cpu().numpy().view(np.uint64), ww[:(t + 63) // 64])
+
+
+# Groups of four blocks: users of at least eight blocks, or whose last group holds two or more.
+GROUP_SIZES = [(1400, 3 * BLOCK + 5), (1100, 4 * BLOCK), (700, 6 * BLOCK), (500, 8 * BLOCK + 62), (460, 9 * BLOCK - 1), (420, 9 * BLOCK + 1025)]
+
+
+def draw_blocks(n, K, seed):
+    """Blocks of short codewords; of 10 to 31 bits a symbol (a window of their own); of more; of both kinds in turn."""
+    s = draw(n, K, seed, False)
+    rng = np.random.default_rng(seed)
+    for b in range((n + BLOCK - 1) // BLOCK):
+        part = s[b * BLOCK:(b + 1) * BLOCK]
+        kind = int(rng.integers(0, 4))
+        if kind and K > 30:
+            lo, hi = ((18, 26), (K - 8, K), (8, 16))[kind - 1]
+            part[:] = rng.integers(lo, hi, part.size)
+    return s
+
+
+@pytest.mark.parametrize("E,M", [(3, 1), (4, 3)])
+@pytest.mark.parametrize("U,n", GROUP_SIZES)
+def test_groups_of_blocks(co3, E, M, U, n):
+    fmt, C = co3.Fmt(E, M), 128
+    w = geometric_weights(fmt.K)
+    lengths = np.asarray(oracle.huffman_lengths(w))
+    codes = oracle.canonical_codes(lengths)
+    rows = [draw_blocks(n, fmt.K, s) for s in (1, 2, 3, 4)]
+    if E == 4:
+        bits = np.concatenate([lengths[r[:n // BLOCK * BLOCK]].reshape(-1, BLOCK).sum(axis=1) for r in rows]) / BLOCK
+        assert (bits < 9).any() and (bits > 31.5).any() and ((bits > 10) & (bits < 31)).any()
+    want = [oracle.encode(s, lengths, codes, C) for s in rows]
+    cap = max((t + 63) // 64 for _, _, t in want) + 2
+    pipe = co3.Co3Pipeline(U, n, fmt, chunk_syms=C, cap_words=cap)
+    fill(pipe, rows, n)
+    pipe.build(torch.from_numpy(np.tile(w.view(np.int32), (U, 1))).cuda())
+    pipe.encode()
+    check(pipe, rows, want, n)
+    assert pipe.poll() == 0
+
+
+@pytest.mark.parametrize("U,n", [(170, 24 * BLOCK + 77), (17, 262 * BLOCK + 1023)])
+def test_groups_of_blocks_under_shared_codes(co3, U, n):
+    fmt, C = co3.Fmt(4, 3), 256
+    # a boundary on a block, one within the look-ahead of a block and one just beyond, one inside a tile, an empty group
+    seg = [0, 5 * BLOCK, 10 * BLOCK + 62, 10 * BLOCK + 62, 15 * BLOCK + 63, n]
+    w = np.stack([np.roll(geometric_weights(fmt.K), 3 * k) for k in range(len(seg) - 1)])
+    lengths = np.stack([np.asarray(oracle.huffman_lengths(x)) for x in w])
+    codes = np.stack([oracle.canonical_codes(x) for x in lengths])
+    rows = [draw_blocks(n, fmt.K, s) for s in (5, 6, 7)]
+    want = [oracle.encode_layers(s, lengths, codes, seg, C) for s in rows]
+    cap = max((t + 63) // 64 for _, _, t in want) + 2
+    pipe = co3.Co3Pipeline(U, n, fmt, chunk_syms=C, cap_words=cap, codes="layer", code_seg_off=seg)
+    fill(pipe, rows, n)
+    pipe.build(torch.from_numpy(w.view(np.int32)).cuda())
+    pipe.encode()
+    check(pipe, rows, want, n)
+    assert pipe.poll() == 0
+
+
+@pytest.mark.parametrize("U,n", [(460, 9 * BLOCK + 62), (700, 6 * BLOCK - 63)])
+def test_groups_of_blocks_two_symbols_per_byte(co3, U, n):
+    test_two_symbols_per_byte(co3, U, n)
+
+
+@pytest.mark.parametrize("short", [1, 65, 2500, 5000])
+def test_groups_of_blocks_beyond_the_capacity(co3, short):
+    """As test_beyond_the_capacity; the end of the capacity lies in a block that could be packed together."""
+    fmt, U, n, C = co3.Fmt(4, 3), 460, 9 * BLOCK + 62, 64
+    w = geometric_weights(fmt.K)
+    lengths = np.asarray(oracle.huffman_lengths(w))
+    codes = oracle.canonical_codes(lengths)
+    row = draw_blocks(n, fmt.K, 8)
+    words, off, total = oracle.encode(row, lengths, codes, C)
+    cap = ((total + 63) // 64 - short) // 2 * 2
+    pipe = co3.Co3Pipeline(U, n, fmt, chunk_syms=C, cap_words=cap)
+    pipe.sym[:, :n] = 0
+    pipe.sym[1, :n] = torch.from_numpy(row).cuda()
+    pipe.words.fill_(-1)
+    pipe.build(torch.from_numpy(np.tile(w.view(np.int32), (U, 1))).cuda())
+    pipe.encode()
+    assert pipe.poll() == -2                                # CO3_ECAP
+    ends = off[16::16].astype(np.int64)                     # of the whole tiles of 1,024
+    last = int((((ends + 63) // 64) <= cap).sum())
+    nw = (int(ends[last - 1]) + 63) // 64
+    got = pipe.words[1].cpu().numpy().view(np.uint64)
+    assert np.array_equal(got[:nw], words[:nw]) and bool((got[nw:] == np.uint64(2**64 - 1)).all())
