@@ -748,17 +748,18 @@ __global__ __launch_bounds__(DE_BLOCK) void k_decode(const uint64_t *__restrict_
 // straddles tensors goes on into the next tensor while that tensor's tables are in the window.  Lanes whose tensor is more than three tensors away
 // from the first one of the range wait for the window: tensors much smaller than a workgroup's range
 // (512 chunks) are better given a code together with a neighbour.
+//
+// The second tables are made for chunks of any size: the 12 bits of the first resolve so much less than the 14 of the
+// per-user decoder that they pay even where a workgroup walks 65 tensors (one user of 300,000 elements in tensors of 2,000,
+// E4M3, chunks of 64, 256: without 107, 1,240 us, with 97, 1,170).
 #define DL_BLOCK 512
 #define DL_SLOTS 4
-#define DL_AHEAD 4
 
-template <bool TILED>
-__global__ __launch_bounds__(DL_BLOCK) __attribute__((amdgpu_waves_per_eu(4))) void k_decode_layers(const uint64_t *__restrict__ words, int64_t cap_words,
-                                                             const uint64_t *__restrict__ chunk_bitoff, int chunk_syms,
-                                                             int64_t nchunks, const void *__restrict__ codes,
-                                                             const int64_t *__restrict__ seg_off, int nseg, int64_t n,
-                                                             uint8_t *__restrict__ sym_out, int64_t stride,
-                                                             int32_t *status)
+template <bool TILED, int AHEAD>
+__global__ __launch_bounds__(DL_BLOCK) __attribute__((amdgpu_waves_per_eu(4)))      // the two workgroups that a unit's LDS holds
+void k_decode_layers(const uint64_t *__restrict__ words, int64_t cap_words, const uint64_t *__restrict__ chunk_bitoff,
+                     int chunk_syms, int64_t nchunks, const void *__restrict__ codes, const int64_t *__restrict__ seg_off,
+                     int nseg, int64_t n, uint8_t *__restrict__ sym_out, int64_t stride, int32_t *status)
 {
     const int u = blockIdx.y;
     __shared__ DecTables t[DL_SLOTS];
@@ -771,7 +772,7 @@ __global__ __launch_bounds__(DL_BLOCK) __attribute__((amdgpu_waves_per_eu(4))) v
     const int64_t c = (int64_t)blockIdx.x * DL_BLOCK + threadIdx.x;
     const bool active = c < nchunks;
     const uint64_t *off = chunk_bitoff + (int64_t)u * (nchunks + 1);
-    LaneStream<DL_AHEAD> ls;
+    LaneStream<AHEAD> ls;
     ls.slot = ring + (threadIdx.x / CO3_WAVE) * (RING_ROWS * RING_ROW_DW) + (threadIdx.x & (CO3_WAVE - 1));
     const int64_t first = c * chunk_syms;
     const int nsym = active ? (int)(n - first < chunk_syms ? n - first : chunk_syms) : 0;
@@ -1079,20 +1080,31 @@ hipError_t co3_launch_decode(const uint64_t *words, int64_t cap_words, const uin
     const int known = co3_device_cus(), cus = known > 0 ? known : 256;
     const bool wide_requests = chunk_syms >= 256 && (nchunks + CO3_WAVE - 1) / CO3_WAVE * U >= 20 * (int64_t)cus;
     const unsigned lblocks = (unsigned)((nchunks + DL_BLOCK - 1) / DL_BLOCK);
+    // Shared codes, whose tables take the LDS of all but two workgroups a unit: the same from half as many wavefronts on,
+    // and where a workgroup decodes more than it walks from tensor to tensor (E4M3, us with 16 | 64 bytes at a time: 4 x
+    // 11 M in tensors of 500,000 elements, chunks of 64 59 | 63, of 128 82 | 77, of 256 98 | 80, of 512 (1,344 wavefronts)
+    // 124 | 127; 10 x 11 M, tensors of 100,000, chunks of 256 200 | 188; 4 x 11 M, tensors of 20,000 and 5,000, chunks of
+    // 256 217 | 227 and 550 | 616; one user of 11 M 66 | 68).
+    const bool wide_layers = chunk_syms >= 128 && (nchunks + CO3_WAVE - 1) / CO3_WAVE * U >= 8 * (int64_t)cus &&
+                             n / (nseg > 0 ? nseg : 1) >= (int64_t)DL_BLOCK * chunk_syms / 4;
 #define CO3_DECODE_LAUNCH(T, P, A)                                                                                 \
     hipLaunchKernelGGL((k_decode<T, P, A>), dim3(blocks, U), dim3(decode_lanes(per_block, P)),                        \
                        (size_t)per_block * RING_ROWS * sizeof(uint32_t), st, words, cap_words, chunk_bitoff, chunk_syms, \
                        nchunks, per_block, codes, code_per_user, n, sym_out, stride, status)
+#define CO3_LAYERS_LAUNCH(T, A)                                                                                    \
+    hipLaunchKernelGGL((k_decode_layers<T, A>), dim3(lblocks, U), dim3(DL_BLOCK), 0, st, words, cap_words, chunk_bitoff, \
+                       chunk_syms, nchunks, codes, seg_off, nseg, n, sym_out, stride, status)
     Co3LaunchTimer tm(CO3_K_DECODE, st);
     // one code for everything, shared by the users: the per-user kernels with every user reading codes[0]
     const int code_per_user = seg_off == nullptr;
     if (seg_off && nseg == 1) seg_off = nullptr;
-    if (seg_off && tiled)
-        hipLaunchKernelGGL(k_decode_layers<true>, dim3(lblocks, U), dim3(DL_BLOCK), 0, st, words, cap_words,
-                           chunk_bitoff, chunk_syms, nchunks, codes, seg_off, nseg, n, sym_out, stride, status);
-    else if (seg_off)
-        hipLaunchKernelGGL(k_decode_layers<false>, dim3(lblocks, U), dim3(DL_BLOCK), 0, st, words, cap_words,
-                           chunk_bitoff, chunk_syms, nchunks, codes, seg_off, nseg, n, sym_out, stride, status);
+    if (seg_off && wide_layers) {
+        if (tiled) CO3_LAYERS_LAUNCH(true, 4);
+        else CO3_LAYERS_LAUNCH(false, 4);
+    } else if (seg_off) {
+        if (tiled) CO3_LAYERS_LAUNCH(true, 0);
+        else CO3_LAYERS_LAUNCH(false, 0);
+    }
     else if (co3_ws_packed(K, chunk_syms, 0)) {
         if (tiled) CO3_DECODE_LAUNCH(true, true, 0);
         else CO3_DECODE_LAUNCH(false, true, 0);
@@ -1104,6 +1116,7 @@ hipError_t co3_launch_decode(const uint64_t *words, int64_t cap_words, const uin
         else CO3_DECODE_LAUNCH(false, false, 0);
     }
 #undef CO3_DECODE_LAUNCH
+#undef CO3_LAYERS_LAUNCH
     return hipGetLastError();
 }
 

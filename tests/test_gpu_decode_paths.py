@@ -75,6 +75,35 @@ def test_requests_of_64_bytes(co3, E, M, n, C, U):
     assert torch.equal(pipe.sym_dec[:, :n], s)
 
 
+# Shared codes of few long tensors on at least eight wavefronts a compute unit: 64 bytes a request, tables from tensor to
+# tensor.  All users hold the same symbols, as many as a power of two: their average is one user's values.
+@pytest.mark.parametrize("n,C,U", [(1_100_001, 128, 16), (2_199_999, 256, 16), (2_199_999, 512, 32)])
+def test_requests_of_64_bytes_under_shared_codes(co3, n, C, U):
+    fmt, f = co3.Fmt(4, 3), oracle.Fmt(4, 3)
+    r = np.random.default_rng(C)
+    seg = [0, n // 5 + 3, n // 2 - 77, n // 2 - 77, n - 70_000, n]
+    p = np.maximum(0.9 ** np.arange(fmt.K), 1e-9)
+    w = np.stack([np.roll(np.maximum(p / p.sum() * 3e9, 1).astype(np.uint32), 5 * k) for k in range(5)])
+    s = np.minimum(np.searchsorted(np.cumsum(p / p.sum()), r.random(n)), fmt.K - 1)
+    at = np.repeat(r.random((n + 39) // 40) < 0.01, 40)[:n]
+    s[at] = r.integers(fmt.K - 8, fmt.K, int(at.sum()))
+    for k in range(5):
+        s[seg[k]:seg[k + 1]] = (s[seg[k]:seg[k + 1]] + 5 * k) % fmt.K
+    s = s.astype(np.uint8)
+    pipe = co3.Co3Pipeline(U, n, fmt, chunk_syms=C, cap_words=(n // 6) // 8 * 8 + 2, codes="layer", code_seg_off=seg)
+    row = torch.from_numpy(s).cuda()
+    pipe.sym[:, :n] = row
+    pipe.build(torch.from_numpy(w.view(np.int32)).cuda())
+    pipe.encode()
+    pipe.decode()
+    pipe.anchor.fill_(2)
+    pipe.aggregate()
+    assert pipe.poll() == 0
+    assert torch.equal(pipe.sym_dec[:, :n], row.expand(U, n))
+    want = oracle.aggregate(s[None], np.array([[2]], np.int32), f)
+    assert np.array_equal(pipe.avg[:n].cpu().numpy().view(np.uint32), want.view(np.uint32))
+
+
 def fibonacci(k):
     w = [1, 1]
     while len(w) < k:
