@@ -194,9 +194,10 @@ struct LaneStream {
 template <int BITS, int ENTRIES2>
 struct DecTablesT {
     static constexpr int kBits = BITS, kEntries2 = ENTRIES2;
+    static constexpr bool kSecond = ENTRIES2 > 1;
     static constexpr int kBits2 = 64 - (DE_REFILL - 1) * BITS < 32 ? 64 - (DE_REFILL - 1) * BITS : 32;
     alignas(16) uint16_t lut[1 << BITS];
-    uint16_t lut2[ENTRIES2];
+    uint16_t lut2[ENTRIES2];      // (1: none)
     uint32_t from2, shift2, n2;   // entry (prefix of 32 bits - from2) >> shift2, below n2 (0: none)
     uint64_t first_code[65];
     uint16_t count[66];
@@ -205,12 +206,11 @@ struct DecTablesT {
     uint64_t lim_incl[65];   // largest 64-bit window (codeword left-aligned, ones below) of a codeword of length <= l
     uint32_t maxlen, lut_bits;
 };
-typedef DecTablesT<CO3_LUT_BITS_MAX, 8> DecTablesPairs;     // beside the two-symbol table
+typedef DecTablesT<CO3_LUT_BITS_MAX, 1> DecTablesPairs;     // beside the two-symbol table
 typedef DecTablesT<CO3_LUT_BITS_MAX, 256> DecTables;      // shared per-layer codes: four of them a workgroup
 
-// second: whether the second table is made (the same for all threads).
 template <class Tables>
-__device__ __forceinline__ void load_tables(Tables &t, const Co3Code *cd, bool second)
+__device__ __forceinline__ void load_tables(Tables &t, const Co3Code *cd)
 {
     constexpr uint32_t BITS = Tables::kBits;
     const uint32_t lb = cd->lut_bits > CO3_LUT_BITS_MAX ? CO3_LUT_BITS_MAX : (cd->lut_bits < 1 ? 1 : cd->lut_bits);
@@ -267,7 +267,7 @@ __device__ __forceinline__ void load_tables(Tables &t, const Co3Code *cd, bool s
             }
         }
     }
-    const bool make2 = second && ml > nb;
+    const bool make2 = Tables::kSecond && ml > nb;
     __syncthreads();
     if (wide != 0u) {
         // the codewords of lengths lb+1 .. nb, a thread each, enter where their prefixes lie
@@ -293,7 +293,7 @@ __device__ __forceinline__ void load_tables(Tables &t, const Co3Code *cd, bool s
             t.lim_incl[l] = lim;
         }
     }
-    if (x == 0 && !make2) t.n2 = t.from2 = t.shift2 = 0u;
+    if (Tables::kSecond && x == 0 && !make2) t.n2 = t.from2 = t.shift2 = 0u;
     if (make2) {
         const int lane = x & (CO3_WAVE - 1);
         const uint64_t end_nb = t.first_code[nb] + t.count[nb];          // uniform
@@ -462,7 +462,7 @@ __device__ __forceinline__ void decode_range(const Tables &t, Stream &ls, int i0
 {
     static_assert(DE_REFILL * Tables::kBits <= 64 && DE_REFILL == 4, "a window holds the lookups between two refills");
     static_assert(DE_GROUP * Tables::kBits < DE_MISS_LEN, "a miss must advance more than a run of hits can");
-    constexpr bool AGAIN = MODE == DE_RETRY;
+    constexpr bool AGAIN = MODE == DE_RETRY, SECOND = Tables::kSecond;
     const int shift = 32 - (int)t.lut_bits;
     int i = i0;
     // cnt < 16 symbols from symbol i on, inside one run
@@ -529,12 +529,15 @@ __device__ __forceinline__ void decode_range(const Tables &t, Stream &ls, int i0
         // Codeword longer than the table prefix, at the start of the window w64: mostly from the second table.  Else the
         // first length whose largest left-aligned codeword is not below the window.  (The limits do not decrease with
         // the length and stay put beyond the longest codeword, so counting the limits below the window gives the
-        // length; without the second table nearly all end within four bits of the prefix, compared without a loop.)  `again`: the window is not known to hold all of it and is read anew for that.
+        // length; without the second table nearly all end within four bits of the prefix, compared without a loop.)
+        // `again`: the window is not known to hold all of it and is read anew for that.
         auto search = [&](uint64_t &w64, bool again) -> uint32_t {
-            const uint32_t i2 = ((uint32_t)(w64 >> 32) - t.from2) >> t.shift2;
-            if (i2 < t.n2) {
-                const uint32_t e2 = t.lut2[i2];
-                if ((e2 >> 8) != DE_MISS_LEN) return e2;
+            if constexpr (SECOND) {
+                const uint32_t i2 = ((uint32_t)(w64 >> 32) - t.from2) >> t.shift2;
+                if (i2 < t.n2) {
+                    const uint32_t e2 = t.lut2[i2];
+                    if ((e2 >> 8) != DE_MISS_LEN) return e2;
+                }
             }
             if (again) w64 = ls.window64(mw = m);
             const uint32_t l0 = t.lut_bits + 1u;
@@ -562,14 +565,22 @@ __device__ __forceinline__ void decode_range(const Tables &t, Stream &ls, int i0
                 uint32_t e = t.lut[(uint32_t)(win >> 32) >> shift];
                 uint32_t drop = e >> 8;
                 if (MODE == DE_LONG && drop == DE_MISS_LEN) {   // skipped by the wavefront when no lane is here
-                    if (mw - m > 64u - Tables::kBits2) win = ls.window64(mw = m);
-                    e = search(win, true);
-                    drop = e >> 8;
-                    // the window is read anew where what is left of it may not hold the lookups to come
-                    if (b + 1 < DE_REFILL && mw - (m - drop) + (DE_REFILL - 1 - b) * Tables::kBits > 64u) {
-                        mw = m - drop;
-                        win = ls.window64(mw);
+                    if constexpr (SECOND) {
+                        if (mw - m > 64u - Tables::kBits2) win = ls.window64(mw = m);
+                        e = search(win, true);
+                        drop = e >> 8;
+                        // the window is read anew where what is left of it may not hold the lookups to come
+                        if (b + 1 < DE_REFILL && mw - (m - drop) + (DE_REFILL - 1 - b) * Tables::kBits > 64u) {
+                            mw = m - drop;
+                            win = ls.window64(mw);
+                            drop = 0u;
+                        }
+                    } else {
+                        win = ls.window64(m);
+                        e = search(win, false);
                         drop = 0u;
+                        mw = m - (e >> 8);
+                        win = ls.window64(mw);
                     }
                 }
                 es[b] = e;
@@ -593,7 +604,7 @@ __device__ __forceinline__ void decode_range(const Tables &t, Stream &ls, int i0
                     if ((e >> 8) == DE_MISS_LEN) {     // (hits since the last read have left win short of bits)
                         win = ls.window64(mw = m);
                         e = search(win, false);
-                        if ((e >> 8) > (uint32_t)Tables::kBits2) win = ls.window64(mw = m - (e >> 8));
+                        if (!SECOND || (e >> 8) > (uint32_t)Tables::kBits2) win = ls.window64(mw = m - (e >> 8));
                         else win <<= e >> 8;
                     } else {
                         win <<= (e >> 8) & 63u;
@@ -673,8 +684,10 @@ __device__ __forceinline__ void decode_chunk_packed(const DecTablesPairs &t, Lan
 // workspace, [U][tiles][chunk_syms/16][64 lanes][16 symbols] with tile = 64 consecutive chunks.
 // PAIRS: the workgroup also builds the two-symbol table (launched for alphabets of at most 16
 // symbols and chunks of at least 32); with TILED the workspace then holds two symbols per byte,
-// [U][tiles][chunk_syms/32][64 lanes][32 symbols in 16 bytes].
-template <bool TILED, bool PAIRS, int AHEAD>
+// [U][tiles][chunk_syms/32][64 lanes][32 symbols in 16 bytes].  SECOND: it makes the second table (larger alphabets, chunks
+// of 256 symbols or more).  Without it a miss is searched as before there was one: with its tests left in (an empty table)
+// 4 x 11.2 M in chunks of 64 took 104.8 us for 103.6, of codewords that all miss 274 for 269 (before: 104, 267).
+template <bool TILED, bool PAIRS, bool SECOND, int AHEAD>
 __global__ __launch_bounds__(DE_BLOCK) void k_decode(const uint64_t *__restrict__ words, int64_t cap_words,
                                                       const uint64_t *__restrict__ chunk_bitoff, int chunk_syms,
                                                       int64_t nchunks, int chunks_per_block, const void *__restrict__ codes,
@@ -685,7 +698,8 @@ __global__ __launch_bounds__(DE_BLOCK) void k_decode(const uint64_t *__restrict_
     // tables first: their LDS offsets then fit the immediate field of the read instructions
     __shared__ struct {
         uint32_t pairs[PAIRS ? (1 << DE_PAIR_BITS) : 1];
-        typename std::conditional<PAIRS, DecTablesPairs, DecTablesT<DE_WIDE_BITS, 256>>::type t;   // one symbol per lookup: the widened table
+        // one symbol per lookup: the widened table
+        typename std::conditional<PAIRS, DecTablesPairs, DecTablesT<DE_WIDE_BITS, SECOND ? 256 : 1>>::type t;
     } lds;
     extern __shared__ __align__(256) uint32_t ring[];   // chunks_per_block * RING_ROWS
     auto &t = lds.t;
@@ -702,8 +716,7 @@ __global__ __launch_bounds__(DE_BLOCK) void k_decode(const uint64_t *__restrict_
     if (active) ls.open(words + (int64_t)u * cap_words, cap_words, p0);
     const int64_t first = c * chunk_syms;
     const int nsym = active ? (int)(n - first < chunk_syms ? n - first : chunk_syms) : 0;
-    const bool second = !PAIRS && chunk_syms >= 256;
-    load_tables(t, dcode_of(codes, code_per_user ? u : 0), second);        // else one code shared by all users
+    load_tables(t, dcode_of(codes, code_per_user ? u : 0));        // else one code shared by all users
     __syncthreads();
     if constexpr (PAIRS) {
         build_pairs<TILED>(t, pairs);
@@ -728,7 +741,7 @@ __global__ __launch_bounds__(DE_BLOCK) void k_decode(const uint64_t *__restrict_
     // symbol alone 54; 10 x 11.2 M E5M2 of one law 98 | 99 | 96.  Smaller chunks scatter more and keep to eight bits.
     auto dense = [&]() -> bool {
         float line = 8.0f;
-        if (second) line = fminf(line, (float)all_bits / (float)n + 8.0f * rsqrtf((float)chunk_syms));
+        if (SECOND) line = fminf(line, (float)all_bits / (float)n + 8.0f * rsqrtf((float)chunk_syms));
         return __any((float)(p1 - p0) > (float)nsym * line) != 0;
     };
     bool ok = true;
@@ -799,10 +812,10 @@ void k_decode_layers(const uint64_t *__restrict__ words, int64_t cap_words, cons
         __syncthreads();                 // nobody reads the slot that is replaced any more
         if (sg == b_lo) {
             for (int k = 0; k < DL_SLOTS - 1 && sg + k <= b_hi; ++k)
-                load_tables(t[(sg + k) & (DL_SLOTS - 1)], dcode_of(codes, sg + k), true);
+                load_tables(t[(sg + k) & (DL_SLOTS - 1)], dcode_of(codes, sg + k));
         }
         if (sg + DL_SLOTS - 1 <= b_hi)
-            load_tables(t[(sg + DL_SLOTS - 1) & (DL_SLOTS - 1)], dcode_of(codes, sg + DL_SLOTS - 1), true);
+            load_tables(t[(sg + DL_SLOTS - 1) & (DL_SLOTS - 1)], dcode_of(codes, sg + DL_SLOTS - 1));
         __syncthreads();
         bool any_long = false;           // uniform
         for (int k = 0; k < DL_SLOTS; ++k) any_long |= t[k].maxlen > t[k].lut_bits;
@@ -1087,8 +1100,8 @@ hipError_t co3_launch_decode(const uint64_t *words, int64_t cap_words, const uin
     // 256 217 | 227 and 550 | 616; one user of 11 M 66 | 68).
     const bool wide_layers = chunk_syms >= 128 && (nchunks + CO3_WAVE - 1) / CO3_WAVE * U >= 8 * (int64_t)cus &&
                              n / (nseg > 0 ? nseg : 1) >= (int64_t)DL_BLOCK * chunk_syms / 4;
-#define CO3_DECODE_LAUNCH(T, P, A)                                                                                 \
-    hipLaunchKernelGGL((k_decode<T, P, A>), dim3(blocks, U), dim3(decode_lanes(per_block, P)),                        \
+#define CO3_DECODE_LAUNCH(T, P, S, A)                                                                              \
+    hipLaunchKernelGGL((k_decode<T, P, S, A>), dim3(blocks, U), dim3(decode_lanes(per_block, P)),                     \
                        (size_t)per_block * RING_ROWS * sizeof(uint32_t), st, words, cap_words, chunk_bitoff, chunk_syms, \
                        nchunks, per_block, codes, code_per_user, n, sym_out, stride, status)
 #define CO3_LAYERS_LAUNCH(T, A)                                                                                    \
@@ -1106,14 +1119,17 @@ hipError_t co3_launch_decode(const uint64_t *words, int64_t cap_words, const uin
         else CO3_LAYERS_LAUNCH(false, 0);
     }
     else if (co3_ws_packed(K, chunk_syms, 0)) {
-        if (tiled) CO3_DECODE_LAUNCH(true, true, 0);
-        else CO3_DECODE_LAUNCH(false, true, 0);
+        if (tiled) CO3_DECODE_LAUNCH(true, true, false, 0);
+        else CO3_DECODE_LAUNCH(false, true, false, 0);
+    } else if (chunk_syms < 256) {
+        if (tiled) CO3_DECODE_LAUNCH(true, false, false, 0);
+        else CO3_DECODE_LAUNCH(false, false, false, 0);
     } else if (wide_requests) {
-        if (tiled) CO3_DECODE_LAUNCH(true, false, 4);
-        else CO3_DECODE_LAUNCH(false, false, 4);
+        if (tiled) CO3_DECODE_LAUNCH(true, false, true, 4);
+        else CO3_DECODE_LAUNCH(false, false, true, 4);
     } else {
-        if (tiled) CO3_DECODE_LAUNCH(true, false, 0);
-        else CO3_DECODE_LAUNCH(false, false, 0);
+        if (tiled) CO3_DECODE_LAUNCH(true, false, true, 0);
+        else CO3_DECODE_LAUNCH(false, false, true, 0);
     }
 #undef CO3_DECODE_LAUNCH
 #undef CO3_LAYERS_LAUNCH
