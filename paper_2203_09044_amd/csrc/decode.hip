@@ -857,7 +857,9 @@ void k_decode_layers(const uint64_t *__restrict__ words, int64_t cap_words, cons
 // per element kept from user to user, and 64-bit comparisons to find its tensor, had brought them to 227.  One user's
 // symbols at a time | as now: one tensor, 32 users of 1 M E3M1 23 | 15.4 us, 16 of 25 M E4M3 121 | 101, 10 of 11.2 M E3M0
 // 28.4 | 27.4; 62 tensors of 11.2 M elements in E4M3, one user 21 | 16.7, two 26.7 | 19.2, four 29 | 24, ten 55 | 45.6; six
-// in E3M0 38 | 30.
+// in E3M0 38 | 30.  Runs that straddle tensors read their symbols by themselves, a user at a time: taking what was requested
+// cost the others more (4 M elements in tensors of 200, ten users E4M3 56 -> 62 us), requesting only where none straddles
+// likewise (two users 16.0 -> 18.5).  In 33,333 tensors of three: E3M0 ten users 54 us.
 template <int TABLE, bool NIB, int PT_AHEAD>
 __global__ __launch_bounds__(PT_WAVES(NIB) * CO3_WAVE)
 __attribute__((amdgpu_waves_per_eu(TABLE == 1 || TABLE == 2 ? (NIB ? 4 : PT_AHEAD == 1 ? 7 : 5) : (NIB ? 3 : 4))))
@@ -1150,10 +1152,14 @@ hipError_t co3_launch_ps_sum_tiled(const uint8_t *symt, int64_t n, int U, int64_
     unsigned blocks = (unsigned)(b < 16384 ? b : 16384);
     Co3LaunchTimer tm(CO3_K_PS_SUM, st);
     const size_t full_bytes = (size_t)U * (size_t)(1 << (1 + fmt.exp_bits + fmt.mant_bits)) * sizeof(float);
-    // Several tensors: the values in LDS pay from three users on (E4M3, us with | without: 11.2 M elements in 62 tensors,
-    // two users 24.1 | 24.5, three 27.9 | 30.6, sixteen 76 | 113; 11 M in 275 tensors, two 27.2 | 25.0, three 32.3 |
-    // 31.6, four 36.7 | 37.8, sixteen 95 | 113).
-    const bool tables_pay = nseg > 1 && U >= 3;
+    // Several tensors: the values of one in LDS pay where a workgroup's steps stay in it and there are users to share what
+    // they cost, which is half the alphabet's values a user (us with | without; 11 M elements in tensors of 400,000: three
+    // users E3M1 24.9 | 25.7, ten 39 | 45, six in E4M3 32.1 | 33.6; of 100,000: three users E3M0 25.5 | 25.8, E4M3 27.4 | 26.7,
+    // eight 37.6 | 38.2; of 40,000: ten in E3M0 46.0 | 46.5, sixteen 60.5 | 61.8, E4M3 62.5 | 61.4; of 15,000: three 34.4 |
+    // 31.5, ten 78 | 75; ResNet-18's 62: three in E3M0 25.1 | 25.4, ten 42.1 | 45.5, E4M3 three 27.2 | 26.4, ten 44.6 | 45.0).
+    const int64_t each = n / (nseg > 0 ? nseg : 1);
+    const bool few_values = fmt.exp_bits + fmt.mant_bits <= 5;
+    const bool tables_pay = nseg > 1 && (few_values ? each >= 32768 && U >= (each >= 65536 ? 3 : 10) : each >= 65536 && U >= 6);
 #define CO3_SUM_LAUNCH(T, P, A, BYTES)                                                                             \
     hipLaunchKernelGGL((k_ps_sum_tiled<T, P, A>), dim3(blocks), dim3(threads), BYTES, st, symt, n, U, ws_stride,  \
                        chunk_syms, nruns, anchor, scale, seg_off, nseg, fmt, acc_in, divisor, avg_out)

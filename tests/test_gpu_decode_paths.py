@@ -269,6 +269,52 @@ def test_average_over_empty_and_single_element_tensors(co3, E, M, U, scaled):
     assert np.array_equal(pipe.avg[:n].cpu().numpy().view(np.uint32), want.view(np.uint32))
 
 
+def encoded(co3, fmt, s, seg, C=256):
+    """A pipeline that holds the streams of the users' symbols s."""
+    U, n = s.shape
+    pipe = co3.Co3Pipeline(U, n, fmt, chunk_syms=C, seg_off=seg)
+    pipe.sym[:, :n] = torch.from_numpy(s).cuda()
+    co3.binding.histogram(pipe.sym, n, fmt, pipe.counts)
+    pipe.build()
+    pipe.encode()
+    return pipe
+
+
+# tensors whose values are kept in LDS: from 65,536 elements each on average and three users (six in 7- and 8-bit formats),
+# from 32,768 and ten; one of too few users and one of too short tensors beside them
+@pytest.mark.parametrize("E,M,U", [(3, 0, 3), (3, 1, 4), (4, 3, 6), (5, 2, 7), (3, 0, 10), (3, 1, 10), (4, 3, 5)])
+@pytest.mark.parametrize("way", ["plain", "multipliers", "continued sum"])
+def test_average_with_a_tensors_values_in_lds(co3, E, M, U, way):
+    fmt, f, B = co3.Fmt(E, M), oracle.Fmt(E, M), co3.binding
+    r = np.random.default_rng(U * 3 + E)
+    sizes = [150_001, 90_000, 7, 120_000, 64] if U < 10 else [60_001, 40_000, 3, 64_000]
+    seg = inp.seg_offsets(sizes)
+    n = int(seg[-1])
+    s = r.integers(0, fmt.K, (U, n)).astype(np.uint8)
+    pipe = encoded(co3, fmt, s, seg)
+    anchor = r.integers(-20, 20, (U, len(sizes))).astype(np.int32)
+    pipe.anchor[:] = torch.from_numpy(anchor)
+    if way == "continued sum":
+        start = r.standard_normal(n).astype(np.float32)
+        acc = torch.nn.functional.pad(torch.from_numpy(start), (0, pipe.stride - n)).cuda()
+        B.ps_aggregate_partial(pipe.words, pipe.chunk_bitoff, 256, pipe.codes, fmt, n, U, pipe.anchor, acc, U + 3, acc, pipe.agg_ws,
+                               pipe.status, seg_off=pipe.seg_off)
+        want = start
+        for u in range(U):
+            want = want + oracle.aggregate(s[u:u + 1], anchor[u:u + 1], f, seg)
+        got, want = acc, want / np.float32(U + 3)
+    elif way == "multipliers":
+        scale = (r.uniform(0.5, 40.0, anchor.shape) * r.choice([-1.0, 1.0], anchor.shape)).astype(np.float32)
+        B.ps_aggregate_scaled(pipe.words, pipe.chunk_bitoff, 256, pipe.codes, fmt, n, U, pipe.anchor, torch.from_numpy(scale).cuda(),
+                              pipe.avg, pipe.agg_ws, pipe.status, seg_off=pipe.seg_off)
+        got, want = pipe.avg, oracle.aggregate(s, anchor, f, seg, scale)
+    else:
+        pipe.aggregate()
+        got, want = pipe.avg, oracle.aggregate(s, anchor, f, seg)
+    assert pipe.poll() == 0
+    assert np.array_equal(got[:n].cpu().numpy().view(np.uint32), want.view(np.uint32))
+
+
 @pytest.mark.parametrize("E,M", [(3, 0), (4, 3)])
 @pytest.mark.parametrize("n", [1, 1024, 16_384, 16_385, 64 * 16_384 - 1, 64 * 16_384, 64 * 16_384 + 1])
 def test_group_offsets_in_the_packer(co3, n, E, M):
