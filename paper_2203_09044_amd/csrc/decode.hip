@@ -860,6 +860,11 @@ void k_decode_layers(const uint64_t *__restrict__ words, int64_t cap_words, cons
 // in E3M0 38 | 30.  Runs that straddle tensors read their symbols by themselves, a user at a time: taking what was requested
 // cost the others more (4 M elements in tensors of 200, ten users E4M3 56 -> 62 us), requesting only where none straddles
 // likewise (two users 16.0 -> 18.5).  In 33,333 tensors of three: E3M0 ten users 54 us.
+//
+// Wavefronts per SIMD that the compiler has to leave room for.  With NIB and a table four (128 registers): with three the
+// long sums slow down (16 x 25 M E3M0 66 -> 75 us), with five registers are stored away (4 x 11.2 M 17.6 -> 20.2).  One
+// user's bytes at a time seven, the most without that (eight: 25 M of one user 25 -> 29 us); four users' five (six 16 x 25 M
+// E4M3 102 -> 106).  Several tensors three and four: what the straddling runs' registers allow.
 template <int TABLE, bool NIB, int PT_AHEAD>
 __global__ __launch_bounds__(PT_WAVES(NIB) * CO3_WAVE)
 __attribute__((amdgpu_waves_per_eu(TABLE == 1 || TABLE == 2 ? (NIB ? 4 : PT_AHEAD == 1 ? 7 : 5) : (NIB ? 3 : 4))))
@@ -1165,9 +1170,10 @@ hipError_t co3_launch_ps_sum_tiled(const uint8_t *symt, int64_t n, int U, int64_
                        chunk_syms, nruns, anchor, scale, seg_off, nseg, fmt, acc_in, divisor, avg_out)
     const size_t half_bytes = full_bytes / 2;
     const int known = co3_device_cus(), cus = known > 0 ? known : 256;
-    // A table of few values, one user at a time where the steps fill the chip anyway (16 x 25 M E3M1, one | four users
-    // at a time: 85.5 | 89 us); two at a time where the registers of more would cost wavefronts.
-    const bool full_chip = blocks >= 16u * (unsigned)cus;
+    // A table of few values: four users at a time; one where there are many that long (E3M1, one | four at a time, four users
+    // of 25 M 36.9 | 34.2 us, sixteen of 18 M 62 | 59.5, of 40 M 130.6 | 128.8, thirty-two of 18 M 111 | 107, but twenty-four
+    // of 25 M 116 | 120, thirty-two 147 | 158).  Two at a time where the registers of more would cost wavefronts.
+    const bool long_sums = U > 16 && blocks >= 20u * (unsigned)cus;
     if (packed) {       // alphabets of at most 16 symbols: the full table is 64 bytes per user
         if (nseg == 1 && U == 1) CO3_SUM_LAUNCH(1, true, 1, full_bytes);
         else if (nseg == 1 && full_bytes <= 4096) CO3_SUM_LAUNCH(1, true, 2, full_bytes);
@@ -1175,7 +1181,7 @@ hipError_t co3_launch_ps_sum_tiled(const uint8_t *symt, int64_t n, int U, int64_
         else if (U == 1) CO3_SUM_LAUNCH(0, true, 1, 0);
         else CO3_SUM_LAUNCH(0, true, 2, 0);
     } else if (nseg == 1 && U == 1) CO3_SUM_LAUNCH(1, false, 1, full_bytes);
-    else if (nseg == 1 && full_bytes <= 4096 && full_chip) CO3_SUM_LAUNCH(1, false, 1, full_bytes);
+    else if (nseg == 1 && full_bytes <= 4096 && long_sums) CO3_SUM_LAUNCH(1, false, 1, full_bytes);
     else if (nseg == 1 && full_bytes <= 4096) CO3_SUM_LAUNCH(1, false, 4, full_bytes);
     else if (nseg == 1 && half_bytes <= 32768) CO3_SUM_LAUNCH(2, false, 4, half_bytes);
     else if (tables_pay && half_bytes <= 32768) CO3_SUM_LAUNCH(3, false, 2, half_bytes);
