@@ -315,6 +315,72 @@ def test_average_with_a_tensors_values_in_lds(co3, E, M, U, way):
     assert np.array_equal(got[:n].cpu().numpy().view(np.uint32), want.view(np.uint32))
 
 
+@pytest.mark.parametrize("E,M,U", [(3, 0, 1), (3, 0, 5), (3, 1, 4), (4, 3, 1), (4, 3, 4), (4, 3, 5), (4, 3, 9)])
+def test_average_with_negative_multipliers(co3, E, M, U):
+    """One tensor: a value is the level divided by the multiplier, sign and all, in every form of the table."""
+    fmt, f = co3.Fmt(E, M), oracle.Fmt(E, M)
+    r = np.random.default_rng(U + E)
+    n = 20_003
+    s = r.integers(0, fmt.K, (U, n)).astype(np.uint8)
+    pipe = encoded(co3, fmt, s, None)
+    anchor = r.integers(-20, 20, (U, 1)).astype(np.int32)
+    scale = (r.uniform(0.5, 40.0, (U, 1)) * np.where(np.arange(U) % 2, 1.0, -1.0)[:, None]).astype(np.float32)
+    pipe.anchor[:] = torch.from_numpy(anchor)
+    co3.binding.ps_aggregate_scaled(pipe.words, pipe.chunk_bitoff, 256, pipe.codes, fmt, n, U, pipe.anchor,
+                                    torch.from_numpy(scale).cuda(), pipe.avg, pipe.agg_ws, pipe.status)
+    assert pipe.poll() == 0
+    want = oracle.aggregate(s, anchor, f, None, scale)
+    assert np.array_equal(pipe.avg[:n].cpu().numpy().view(np.uint32), want.view(np.uint32))
+
+
+# runs inside a tensor take a value as the code's bits times a power of two where that is exact, from the conversion's lowest
+# anchor to its highest; one below it they do not
+@pytest.mark.parametrize("E,M", [(1, 2), (3, 0), (3, 1), (4, 3), (5, 2), (7, 0)])
+@pytest.mark.parametrize("U", [1, 2, 5])
+def test_average_at_the_ends_of_the_anchors(co3, E, M, U):
+    fmt, f = co3.Fmt(E, M), oracle.Fmt(E, M)
+    r = np.random.default_rng(U)
+    low = (1 << E) - 1 - 126
+    ends = [low - 1, low, low + 1, 0, 125, 126, 127]
+    seg = inp.seg_offsets([2000] * len(ends))
+    n = int(seg[-1])
+    s = r.integers(0, fmt.K, (U, n)).astype(np.uint8)
+    s[1:, int(seg[4]):] = 0                       # sums of the largest levels stay finite
+    s[:, :64] = 1                                 # the smallest level
+    s[0, -64:] = fmt.K // 2 - 1                   # the largest
+    pipe = encoded(co3, fmt, s, seg)
+    anchor = np.tile(np.array(ends, np.int32), (U, 1))
+    pipe.anchor[:] = torch.from_numpy(anchor)
+    pipe.aggregate()
+    assert pipe.poll() == 0
+    want = oracle.aggregate(s, anchor, f, seg)
+    assert np.isfinite(want).all() and np.abs(want).max() >= 2.0 ** 127 / U and np.abs(want[want != 0]).min() <= 2.0 ** -126
+    assert np.array_equal(pipe.avg[:n].cpu().numpy().view(np.uint32), want.view(np.uint32))
+
+
+@pytest.mark.parametrize("E,M", [(3, 0), (4, 3)])
+@pytest.mark.parametrize("U", [1, 2, 5])
+def test_average_of_extreme_tensors(co3, E, M, U):
+    """Tensors of zeros, of subnormal numbers and of one user's values near the largest float, through a whole iteration."""
+    fmt, f = co3.Fmt(E, M), oracle.Fmt(E, M)
+    r = np.random.default_rng(U)
+    sizes = [3000, 2001, 5, 4096, 900]
+    seg = inp.seg_offsets(sizes)
+    n = int(seg[-1])
+    g = (r.standard_normal((U, n)) * np.repeat([0.0, 1e-41, 1e-38, 1.0, 0.0], sizes)).astype(np.float32)
+    g[0, int(seg[4]):] = (r.uniform(-1.0, 1.0, sizes[4]) * 3.3e38).astype(np.float32)
+    pipe = co3.Co3Pipeline(U, n, fmt, seg_off=seg)
+    buf = pipe.new_gradient_buffer()
+    buf[:, :n] = torch.from_numpy(g).cuda()
+    pipe.step(buf)
+    assert pipe.poll() == 0
+    A = np.stack([oracle.anchor(g[u], f, seg) for u in range(U)])
+    assert A.min() == (1 << E) - 1 - 126 and A.max() == 127
+    sym = np.stack([oracle.convert_ef(g[u], np.zeros(n, np.float32), A[u], 1.0, f, seg)[0] for u in range(U)])
+    want = oracle.aggregate(sym, A, f, seg)
+    assert np.array_equal(pipe.avg[:n].cpu().numpy().view(np.uint32), want.view(np.uint32))
+
+
 @pytest.mark.parametrize("E,M", [(3, 0), (4, 3)])
 @pytest.mark.parametrize("n", [1, 1024, 16_384, 16_385, 64 * 16_384 - 1, 64 * 16_384, 64 * 16_384 + 1])
 def test_group_offsets_in_the_packer(co3, n, E, M):
