@@ -315,7 +315,8 @@ __device__ __forceinline__ void load_tables(Tables &t, const Co3Code *cd)
             const uint32_t mine = end < from ? 0u : end - from > 0xffffull ? 0xffffu : (uint32_t)(end - from);
             for (uint32_t i = (uint32_t)xr; i < n2; i += step) {
                 uint32_t l = nb + 1u;
-                for (uint32_t k = nb + 1u; k <= top; ++k) l += i >= (uint32_t)__builtin_amdgcn_readlane((int)mine, (int)k) ? 1u : 0u;
+                for (uint32_t k = nb + 1u; k <= top; ++k)
+                    l += i >= (uint32_t)__builtin_amdgcn_readlane((int)mine, (int)k) ? 1u : 0u;
                 uint32_t e = DE_MISS_LEN << 8;
                 if (l <= top) {
                     const uint64_t off = ((from + i) >> (top - l)) - t.first_code[l];
@@ -738,7 +739,10 @@ __global__ __launch_bounds__(DE_BLOCK) void k_decode(const uint64_t *__restrict_
     // eight bits a symbol, or half a bit a symbol more than the stream on average (chunks of 512: a third).  Chunks of
     // data that the code was made for scatter by a tenth to an eighth of a bit (256 symbols); those of tensors that it
     // was not made for lie beyond: one user's ResNet-18 in E4M3 44 us; with a line of 0.63 bits 53, of eight bits a
-    // symbol alone 54; 10 x 11.2 M E5M2 of one law 98 | 99 | 96.  Smaller chunks scatter more and keep to eight bits.
+    // symbol alone 54; 10 x 11.2 M E5M2 of one law 98 | 99 | 96.  Five other layouts of 7 to 62 tensors whose scales lie
+    // three decades apart, with this line | eight bits alone: E4M3 41 | 49, 69 | 69, 42 | 42, 59 | 59, 44 | 48 us, E5M2 44 |
+    // 50, 80 | 85, 36 | 38, 50 | 50, 41 | 45; in E4M1, where a chunk is dense with fewer codewords beyond the table, 32.4 |
+    // 30.3, 79 | 80, 31 | 29, 34 | 32, 36 | 38.  Smaller chunks scatter more and keep to eight bits.
     auto dense = [&]() -> bool {
         float line = 8.0f;
         if (SECOND) line = fminf(line, (float)all_bits / (float)n + 8.0f * rsqrtf((float)chunk_syms));
@@ -758,9 +762,10 @@ __global__ __launch_bounds__(DE_BLOCK) void k_decode(const uint64_t *__restrict_
 // (tensor s in slot s mod 4): a lane decodes the part of its chunk that lies in the tensor at its
 // position as soon as that tensor's tables are there, so the chunks on both sides of a tensor
 // boundary are decoded at the same time, each lane reading the table of its own tensor; a chunk that
-// straddles tensors goes on into the next tensor while that tensor's tables are in the window.  Lanes whose tensor is more than three tensors away
-// from the first one of the range wait for the window: tensors much smaller than a workgroup's range
-// (512 chunks) are better given a code together with a neighbour.
+// straddles tensors goes on into the next tensor while that tensor's tables are in the window.  Lanes
+// whose tensor is more than three tensors away from the first one of the range wait for the window:
+// tensors much smaller than a workgroup's range (512 chunks) are better given a code together with a
+// neighbour.
 //
 // The second tables are made for chunks of any size: the 12 bits of the first resolve so much less than the 14 of the
 // per-user decoder that they pay even where a workgroup walks 65 tensors (one user of 300,000 elements in tensors of 2,000,
@@ -768,8 +773,9 @@ __global__ __launch_bounds__(DE_BLOCK) void k_decode(const uint64_t *__restrict_
 #define DL_BLOCK 512
 #define DL_SLOTS 4
 
+// Compiled for the two workgroups that a unit's LDS holds.
 template <bool TILED, int AHEAD>
-__global__ __launch_bounds__(DL_BLOCK) __attribute__((amdgpu_waves_per_eu(4)))      // the two workgroups that a unit's LDS holds
+__global__ __launch_bounds__(DL_BLOCK) __attribute__((amdgpu_waves_per_eu(4)))
 void k_decode_layers(const uint64_t *__restrict__ words, int64_t cap_words, const uint64_t *__restrict__ chunk_bitoff,
                      int chunk_syms, int64_t nchunks, const void *__restrict__ codes, const int64_t *__restrict__ seg_off,
                      int nseg, int64_t n, uint8_t *__restrict__ sym_out, int64_t stride, int32_t *status)
@@ -969,7 +975,8 @@ void k_ps_sum_tiled(const uint8_t *__restrict__ symt, int64_t n, int U, int64_t 
             from_table = bs == co3_find_seg(seg_off, nseg, b1 < n ? b1 : n - 1);     // the same for all threads
             if (from_table && bs != table_seg) {       // (every read of the last values lies before a barrier below)
                 const int sh = EM + (HALF ? 0 : 1);            // (K is a power of two)
-                for (int j = threadIdx.x; j < U << sh; j += PT_BLOCK) value_of[j] = value((uint32_t)j & ((1u << sh) - 1u), j >> sh, bs);
+                for (int j = threadIdx.x; j < U << sh; j += PT_BLOCK)
+                    value_of[j] = value((uint32_t)j & ((1u << sh) - 1u), j >> sh, bs);
                 table_seg = bs;
                 __syncthreads();
             }

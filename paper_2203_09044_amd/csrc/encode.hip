@@ -455,16 +455,16 @@ __device__ __forceinline__ void pack_put(PackLds &L, uint64_t v, uint32_t nb, ui
     if ((d & 63u) + nb > 64u) atomicOr(w + 1, (unsigned long long)(v >> ((0u - d) & 63u)));
 }
 
-// Up to `blocks` blocks from element i0 on, all of one code.  where(request(lane), tid, group_base, group_end): stream positions of their
-// group of tiles and of its end (called behind the first barrier, when what it is made from has arrived with the symbols
-// and the table); toff: positions of their tiles in the group, up to tile `tiles_end` (from the first block's on), where
-// the group ends.  Takes the blocks up to the first one that does not fit a window or ends behind the stream's capacity;
-// a first one that fits the whole array alone.  Returns their number (to all threads).
+// Up to `blocks` blocks from element i0 on, all of one code.  where(request(lane), tid, group_base, group_end): stream
+// positions of their group of tiles and of its end (made behind the first barrier, when what is requested beside the
+// symbols and the table has arrived); toff: positions of their tiles in the group, up to tile `tiles_end` (from the
+// first block's on), where the group ends.  Takes the blocks up to the first one that does not fit a window or ends
+// behind the stream's capacity; a first one that fits the whole array alone.  Returns their number (to all threads).
 template <bool NIB, class Request, class Where>
 __device__ __forceinline__ int pack_blocks(PackLds &L, const uint8_t *su, const Co3Code *cd, int K, int64_t n, int64_t i0,
-                                            int blocks, int wave, int tid, Request request, Where where, const uint64_t *__restrict__ toff,
-                                            int tiles_end, uint64_t *__restrict__ wu, int64_t cap_words, int chunk_syms,
-                                            uint64_t *__restrict__ chunk_off)
+                                            int blocks, int wave, int tid, Request request, Where where,
+                                            const uint64_t *__restrict__ toff, int tiles_end, uint64_t *__restrict__ wu,
+                                            int64_t cap_words, int chunk_syms, uint64_t *__restrict__ chunk_off)
 {
     constexpr int G = EN_LSYM / 4;
     const int lane = tid & (CO3_WAVE - 1);
@@ -499,7 +499,8 @@ __device__ __forceinline__ int pack_blocks(PackLds &L, const uint8_t *su, const 
         } else {
             L.tab[j] = pack_entry(e >> 6, (uint32_t)(e & 63u));
         }
-        for (int q = j; q < EN_WG_WORDS + 2; q += EN_BLOCK) reinterpret_cast<ulonglong2 *>(L.win)[q] = make_ulonglong2(0ull, 0ull);
+        for (int q = j; q < EN_WG_WORDS + 2; q += EN_BLOCK)
+            reinterpret_cast<ulonglong2 *>(L.win)[q] = make_ulonglong2(0ull, 0ull);
     }
     __syncthreads();
     uint64_t group_base, group_end;
@@ -513,9 +514,10 @@ __device__ __forceinline__ int pack_blocks(PackLds &L, const uint8_t *su, const 
         const uint64_t cap_bits = (uint64_t)cap_words * 64u;
         const uint64_t left = cap_bits > group_base ? cap_bits - group_base : 0ull;
         const uint32_t most = left < 0xffffffffull ? (uint32_t)left : 0xffffffffu;
-        // lane 4 k: the end of block k, from the lane four on (a group has 16 tiles, a row of lanes: its last block ends with it)
+        // lane 4 k: the end of block k, from the lane four on (row_shl:4; a group has 16 tiles, a row of lanes: its last
+        // block ends with it)
         static_assert(CO3_PACK_GROUP == 16 && EN_WAVES == 4, "a block's end lies four lanes on in a row of 16");
-        const uint32_t to = (uint32_t)__builtin_amdgcn_update_dpp((int)last_off, (int)offs, 0x104, 0xf, 0xf, false);   // row_shl:4
+        const uint32_t to = (uint32_t)__builtin_amdgcn_update_dpp((int)last_off, (int)offs, 0x104, 0xf, 0xf, false);
         const uint32_t size = to - offs;
         const uint32_t fits = (uint32_t)__ballot(to <= most && size <= EN_WG_WORDS * 64u - 63u);
         const int fit = __builtin_ctz((~fits & 0x1111u) | 0x10000u) / EN_WAVES;
@@ -634,8 +636,8 @@ __device__ __forceinline__ int pack_blocks(PackLds &L, const uint8_t *su, const 
 // The general path: a wavefront packs its own tile tb, of any size and with any codes, through a window of its own.
 // s: the lane's 16 symbols, four a word; raw: a complete tile of symbols stored two per byte stays in that form, one
 // lookup per byte; next_sym: the symbols that follow the tile (their codewords complete its last word).
-__device__ __forceinline__ void load_tile(const uint8_t *su, bool nib, int64_t n, int64_t tb, int lane, uint32_t (&s)[4], uint2 &raw,
-                                          int &nvalid, uint32_t &next_sym, bool &has_next)
+__device__ __forceinline__ void load_tile(const uint8_t *su, bool nib, int64_t n, int64_t tb, int lane, uint32_t (&s)[4],
+                                          uint2 &raw, int &nvalid, uint32_t &next_sym, bool &has_next)
 {
     const int64_t t0 = tb * CO3_PACK_SYMS;               // the wavefront's tile: elements [t0, t1)
     const int64_t t1 = t0 + CO3_PACK_SYMS < n ? t0 + CO3_PACK_SYMS : n;
@@ -653,11 +655,11 @@ __device__ __forceinline__ void load_tile(const uint8_t *su, bool nib, int64_t n
 // LAYERS: a tile that straddles tensors (look-ahead included) reads its entries from the code blobs, tensor by element.
 // STAGE: words of the window; a tile of short codewords uses EN_STAGE_WORDS of them.
 template <bool LAYERS, int STAGE>
-__device__ __forceinline__ void pack_tile(const uint32_t (&s)[4], uint2 raw, int nvalid, uint32_t next_sym, bool has_next, bool nib,
-                                          int64_t n, const void *codes, int K, const int64_t *seg_off, int nseg, int64_t tb, int lane,
-                                          uint64_t *enc_s, const uint64_t *penc_s,
-                                          unsigned long long *stage, uint32_t maxlen, uint64_t B0, uint64_t *wu, int64_t cap_words,
-                                          int chunk_syms, uint64_t *chunk_off)
+__device__ __forceinline__ void pack_tile(const uint32_t (&s)[4], uint2 raw, int nvalid, uint32_t next_sym, bool has_next,
+                                          bool nib, int64_t n, const void *codes, int K, const int64_t *seg_off, int nseg,
+                                          int64_t tb, int lane, uint64_t *enc_s, const uint64_t *penc_s,
+                                          unsigned long long *stage, uint32_t maxlen, uint64_t B0, uint64_t *wu,
+                                          int64_t cap_words, int chunk_syms, uint64_t *chunk_off)
 {
     const int64_t t0 = tb * CO3_PACK_SYMS;
     const int64_t t1 = t0 + CO3_PACK_SYMS < n ? t0 + CO3_PACK_SYMS : n;
@@ -831,7 +833,8 @@ __device__ __forceinline__ void pack_tile(const uint32_t (&s)[4], uint2 raw, int
 }
 
 // The user's codewords for the general path; called by all threads of the workgroup.  Returns the longest length.
-__device__ __forceinline__ uint32_t load_tile_tables(uint64_t *enc_s, uint64_t *penc_s, const Co3Code *cd, int K, bool nib, int tid)
+__device__ __forceinline__ uint32_t load_tile_tables(uint64_t *enc_s, uint64_t *penc_s, const Co3Code *cd, int K, bool nib,
+                                                     int tid)
 {
     for (int j = tid; j < 256; j += EN_BLOCK) {
         enc_s[j] = j < K ? cd->enc[j] : 0ull;
@@ -960,7 +963,8 @@ void k_enc_pack_blocks(const uint8_t *__restrict__ sym, int64_t n, int64_t strid
             group_end = (uint32_t)__builtin_amdgcn_readlane((int)upto, (int)grp);
         } else {
             auto of_lane = [&](int l) -> uint64_t {
-                return (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)hi, l) << 32 | (uint32_t)__builtin_amdgcn_readlane((int)lo, l);
+                const uint32_t h = (uint32_t)__builtin_amdgcn_readlane((int)hi, l);
+                return (uint64_t)h << 32 | (uint32_t)__builtin_amdgcn_readlane((int)lo, l);
             };
             group_base = of_lane(0);
             group_end = of_lane(1);
@@ -1003,7 +1007,8 @@ void k_enc_pack_blocks(const uint8_t *__restrict__ sym, int64_t n, int64_t strid
             if (together || (!LAYERS && apart)) __syncthreads();
             together = false;
             apart = true;
-            const uint32_t maxlen = LAYERS ? 0u : load_tile_tables(lds.tile.enc_all, lds.tile.penc_s, code_of(codes, u), K, NIB, tid);
+            uint32_t maxlen = 0u;
+            if (!LAYERS) maxlen = load_tile_tables(lds.tile.enc_all, lds.tile.penc_s, code_of(codes, u), K, NIB, tid);
             if (!LAYERS) __syncthreads();
             const uint64_t requested = request(lane);
             const int64_t tb = tb0 + k * EN_WAVES + wave;
@@ -1016,10 +1021,10 @@ void k_enc_pack_blocks(const uint8_t *__restrict__ sym, int64_t n, int64_t strid
             uint64_t group_base, group_end;
             where(requested, tid, group_base, group_end);
             if (tb < nblk)
-                pack_tile<LAYERS, EN_LONG_STAGE_WORDS>(s, raw, nvalid, next_sym, has_next, NIB, n, codes, K, seg_off, nseg, tb, lane,
-                                                       lds.tile.enc_all + (LAYERS ? wave * 256 : 0), lds.tile.penc_s,
-                                                       lds.tile.stage_all[wave], maxlen, group_base + tile_base, wu, cap_words,
-                                                       chunk_syms, chunk_off);
+                pack_tile<LAYERS, EN_LONG_STAGE_WORDS>(
+                    s, raw, nvalid, next_sym, has_next, NIB, n, codes, K, seg_off, nseg, tb, lane,
+                    lds.tile.enc_all + (LAYERS ? wave * 256 : 0), lds.tile.penc_s, lds.tile.stage_all[wave], maxlen,
+                    group_base + tile_base, wu, cap_words, chunk_syms, chunk_off);
         }
         k += m;
     }
@@ -1079,7 +1084,8 @@ hipError_t co3_launch_encode(const uint8_t *sym, int64_t n, int U, int64_t strid
     }
     static_assert((int64_t)CO3_WAVE * CO3_PACK_GROUP * CO3_PACK_SYMS * 64 < (1ll << 32), "64 groups fit 32 bits");
     const bool scan_in_pack = !seg_off && nblk > 0 && ngrp <= CO3_WAVE;
-    if (!scan_in_pack && co3_launch_enc_scan(groupsum, ngrp, U, cap_words, chunk_bitoff, nchunks, total_bits, status, st) != hipSuccess)
+    if (!scan_in_pack &&
+        co3_launch_enc_scan(groupsum, ngrp, U, cap_words, chunk_bitoff, nchunks, total_bits, status, st) != hipSuccess)
         return hipGetLastError();
     if (nblk > 0) {
         const bool groups = pack_by_groups(n, U, seg_off ? nseg : 0);
