@@ -1,7 +1,8 @@
-"""The packer where a workgroup takes several blocks of four tiles in a row (batches of at least 4,096 such blocks): ends
-on, before and behind a block, codewords and pairs of codewords beyond its 32-bit table entries, blocks beyond its window,
-streams beyond their capacity, codes per user and per group of tensors, symbols a byte and two per byte.  Every word is
-defined; the oracle packs some of the users, and the others are equal to them."""
+"""The packer in batches of at least 4,096 blocks of four tiles, where a workgroup takes groups of four blocks if the users'
+vectors hold whole ones, and a tile per wavefront if not: ends on, before and behind a block, codewords and pairs of
+codewords beyond its 32-bit table entries, blocks beyond its window, streams beyond their capacity, codes per user and per
+group of tensors, symbols a byte and two per byte.  Every word is defined; the oracle packs some of the users, and the
+others are equal to them."""
 import numpy as np
 import pytest
 
@@ -53,7 +54,8 @@ def check(pipe, rows, want, n):
         assert torch.equal(got, torch.from_numpy(off.view(np.int64)).cuda().expand_as(got))
 
 
-# 2 blocks a workgroup from 4,096 blocks on, 4 from 16,384; the last two with more than 64 groups of tiles
+# users of few blocks (those of a group and a little more take a tile per wavefront); the last two with more than 64
+# groups of tiles
 SIZES = [(2050, 2 * BLOCK), (2050, 2 * BLOCK - 1), (1400, 2 * BLOCK + 1), (1100, 4 * BLOCK - 1025), (900, 4 * BLOCK + 62),
          (4100, 4 * BLOCK), (3300, 4 * BLOCK + 1), (2800, 6 * BLOCK - 63), (17, 262 * BLOCK + 1023), (64, 257 * BLOCK)]
 
