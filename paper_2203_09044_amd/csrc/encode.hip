@@ -419,7 +419,7 @@ __device__ __forceinline__ void stage_bits(unsigned long long *stage, int64_t wi
 // is handed to the window of the next.  What is the same for a wavefront is kept in scalar registers, and codewords are
 // joined in table entries of 32 bits (16 symbols of a lane: 267 -> 175 vector instructions in an 8-bit format, 237 -> 117
 // with two symbols per byte).  Fewer instructions alone gave nothing: a workgroup per block with the same packing took
-// 198 and 49 us below.  10 x 11.2 M E3M0 52 -> 35.5 us, E4M3 57 -> 46; 16 x 25 M E4M3 199 -> 158 (737 MB at 4.7 TB/s, the
+// 198 and 49 us below.  10 x 11.2 M E3M0 52 -> 34 us, E4M3 57 -> 46; 16 x 25 M E4M3 199 -> 158 (737 MB at 4.7 TB/s, the
 // rate of a copy); 4 x 11.2 M E4M3 under shared codes 50 -> 31.
 //
 // A block of more than 10 bits a symbol takes the windows' LDS alone (encoding 10 x 11.2 M in E4M3, a fifth | all of the
